@@ -1249,7 +1249,33 @@ __global__ __launch_bounds__(512) void gemm_dma_pers_kernel(GemmParams p) {
 // output tile (64 rows) on its way out
 constexpr int kDmaMnSlotB = 64 * (256 * 4 + 16);   // >= kDmaStageB, one fp32 quarter tile
 
-template <bool OUT_BF16>
+// Byte offset, from the stage's first k row, of a chunk that a full stage
+// loads at offset off (k row kr of rows ld bytes apart), in a last stage of
+// only rem k rows: rows past the end load the last row again.
+__device__ __forceinline__ uint32_t tail_offset(uint32_t off, int kr, int rem, int64_t ld) {
+    return kr < rem ? off : off - uint32_t((kr - rem + 1) * ld);
+}
+
+// k rows rem .. KT - 1 of both operand tiles of a stage (512-byte rows, B
+// at st + opb) set to zero by NT threads, so that a last stage short of KT
+// rows adds nothing past its end (also where the repeated rows hold
+// infinities or NaN).  Between the barrier that the loads have landed
+// behind and the reads.
+template <int KT, int NT>
+__device__ __forceinline__ void zero_tail(char *st, int opb, int rem, int tid) {
+    const u32x4 z = {0, 0, 0, 0};
+    for (int i = rem * 32 + tid; i < KT * 32; i += NT) {
+        *reinterpret_cast<u32x4 *>(st + i * 16) = z;
+        *reinterpret_cast<u32x4 *>(st + opb + i * 16) = z;
+    }
+    __syncthreads();
+}
+
+// TAIL: K is not a whole number of stages (an odd token count): the last
+// stage of the last split is loaded with its rows clamped and its missing
+// rows zeroed in LDS, one short pass more.  Without it such a product had
+// only the bounds-checked kernel: 768 x 768 x 16001, 70 us there, 32 us here.
+template <bool OUT_BF16, bool TAIL>
 __global__ __launch_bounds__(512) void gemm_dma_mn_kernel(GemmParams p) {
     static_assert(kDmaMnSlotB >= kDmaStageB, "slot size");
     constexpr int BM = 256, BN = 256, WM = 128, WN = 64, NT = 512, KT = kDmaKT;
@@ -1264,7 +1290,8 @@ __global__ __launch_bounds__(512) void gemm_dma_mn_kernel(GemmParams p) {
     const int64_t m0 = ti.row * BM, n0 = ti.col * BN;
     const int64_t kbeg = ti.z * p.kchunk;
     const int64_t kend = min(p.K, kbeg + p.kchunk);
-    const int ntiles = kend > kbeg ? int((kend - kbeg) / KT) : 0;
+    const int ntiles = kend > kbeg ? int((kend - kbeg + (TAIL ? KT - 1 : 0)) / KT) : 0;
+    const int rem = TAIL && kend > kbeg ? int((kend - kbeg) % KT) : 0;   // k rows of a short last stage
     const char *abase = reinterpret_cast<const char *>(p.A) + kbeg * p.lda * ESZ;
     const char *bbase = reinterpret_cast<const char *>(p.B) + kbeg * p.ldb * ESZ;
     const int64_t astep = KT * p.lda * ESZ, bstep = KT * p.ldb * ESZ;
@@ -1279,7 +1306,27 @@ __global__ __launch_bounds__(512) void gemm_dma_mn_kernel(GemmParams p) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    if (ntiles > 0) dma_issue<4>(slot0, abase, bbase, aoffs, boffs, wave);
+    auto issue = [&](char *slot, int kt) {
+        if constexpr (TAIL) {
+            if (rem && kt == ntiles - 1) {
+                uint32_t ta[4], tb[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int kr = (wave * 4 + j) * 2 + (lane >> 5);
+                    ta[j] = tail_offset(aoffs[j], kr, rem, p.lda * ESZ);
+                    tb[j] = tail_offset(boffs[j], kr, rem, p.ldb * ESZ);
+                }
+                dma_issue<4>(slot, abase + kt * astep, bbase + kt * bstep, ta, tb, wave);
+                return;
+            }
+        }
+        dma_issue<4>(slot, abase + kt * astep, bbase + kt * bstep, aoffs, boffs, wave);
+    };
+    auto fix = [&](char *slot, int kt) {
+        if constexpr (TAIL)
+            if (rem && kt == ntiles - 1) zero_tail<KT, NT>(slot, kDmaOpB, rem, tid);
+    };
+    if (ntiles > 0) issue(slot0, 0);
     for (int i = tid; i < BM; i += NT) roff[i] = m0 + i < p.M ? remap(p.rmap, m0 + i) : int64_t(-1);
     for (int i = tid; i < BN; i += NT) coff[i] = n0 + i < p.N ? remap(p.cmap, n0 + i) : int64_t(-1);
 
@@ -1300,11 +1347,13 @@ __global__ __launch_bounds__(512) void gemm_dma_mn_kernel(GemmParams p) {
 
     for (int kt = 0; kt < ntiles; kt += 2) {
         dma_stage_barrier();
-        if (kt + 1 < ntiles) dma_issue<4>(slot1, abase + (kt + 1) * astep, bbase + (kt + 1) * bstep, aoffs, boffs, wave);
+        if (kt + 1 < ntiles) issue(slot1, kt + 1);
+        fix(slot0, kt);
         dma_mma<true, TM, TN>(acc, slot0, aaddr, baddr, kpos);
         if (kt + 1 >= ntiles) break;
         dma_stage_barrier();
-        if (kt + 2 < ntiles) dma_issue<4>(slot0, abase + (kt + 2) * astep, bbase + (kt + 2) * bstep, aoffs, boffs, wave);
+        if (kt + 2 < ntiles) issue(slot0, kt + 2);
+        fix(slot1, kt + 1);
         dma_mma<true, TM, TN>(acc, slot1, aaddr, baddr, kpos);
     }
     __syncthreads();   // every wave is done with the operand slots
@@ -1379,6 +1428,8 @@ constexpr int kD32KT = 32;                  // k per stage
 constexpr int kD32Op = 128 * kD32KT * 4;    // one operand tile (16 KB)
 constexpr int kD32Stage = 2 * kD32Op;       // A and B of one stage
 
+// TAIL: K not a whole number of stages, as in gemm_dma_mn_kernel.
+template <bool TAIL>
 __global__ __launch_bounds__(256) void gemm_dma32_kernel(GemmParams p) {
     constexpr int BM = 128, BN = 128, WM = 64, WN = 64, TM = 2, TN = 2, NT = 256;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1389,7 +1440,8 @@ __global__ __launch_bounds__(256) void gemm_dma32_kernel(GemmParams p) {
     const TileIdx ti = tile_of(p);
     const int64_t m0 = ti.row * BM, n0 = ti.col * BN;
     const int64_t k0 = ti.z * p.kchunk, k1 = min(p.K, k0 + p.kchunk);
-    const int ntiles = k1 > k0 ? int((k1 - k0) / kD32KT) : 0;
+    const int ntiles = k1 > k0 ? int((k1 - k0 + (TAIL ? kD32KT - 1 : 0)) / kD32KT) : 0;
+    const int rem = TAIL && k1 > k0 ? int((k1 - k0) % kD32KT) : 0;   // k rows of a short last stage
     const char *abase = reinterpret_cast<const char *>(p.A);
     const char *bbase = reinterpret_cast<const char *>(p.B);
     // byte offsets of this thread's four chunks of A and of B in one stage
@@ -1408,6 +1460,21 @@ __global__ __launch_bounds__(256) void gemm_dma32_kernel(GemmParams p) {
     auto issue = [&](char *st, int kt) {
         char *sa = st + wave * 4 * 1024, *sb = st + kD32Op + wave * 4 * 1024;
         const char *ga = abase + kt * astep, *gb = bbase + kt * bstep;
+        if constexpr (TAIL) {
+            if (rem && kt == ntiles - 1) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int kr = (wave * 4 + j) * 2 + (lane >> 5);
+                    __builtin_amdgcn_global_load_lds(
+                        reinterpret_cast<const void *>(ga + tail_offset(aoffs[j], kr, rem, p.lda * 4)),
+                        (lds_void_t *)(sa + j * 1024), 16, 0, 0);
+                    __builtin_amdgcn_global_load_lds(
+                        reinterpret_cast<const void *>(gb + tail_offset(boffs[j], kr, rem, p.ldb * 4)),
+                        (lds_void_t *)(sb + j * 1024), 16, 0, 0);
+                }
+                return;
+            }
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             __builtin_amdgcn_global_load_lds(reinterpret_cast<const void *>(ga + aoffs[j]),
@@ -1433,7 +1500,9 @@ __global__ __launch_bounds__(256) void gemm_dma32_kernel(GemmParams p) {
     for (int kt = 0; kt < ntiles; ++kt) {
         dma_stage_barrier();
         if (kt + 1 < ntiles) issue(smem + ((kt + 1) & 1) * kD32Stage, kt + 1);
-        const char *st = smem + (kt & 1) * kD32Stage;
+        char *st = smem + (kt & 1) * kD32Stage;
+        if constexpr (TAIL)
+            if (rem && kt == ntiles - 1) zero_tail<kD32KT, NT>(st, kD32Op, rem, tid);
         // k rows of 512 bytes; lane (lr, lh) reads m = lr of k row 2 s + lh
         const float *fa = reinterpret_cast<const float *>(st), *fb = reinterpret_cast<const float *>(st + kD32Op);
 #pragma unroll
@@ -1456,10 +1525,11 @@ __global__ __launch_bounds__(256) void gemm_dma32_kernel(GemmParams p) {
     epilogue<false, TM, TN, WM, WN, true>(p, acc, roff, coff, wm, wn, lr, lh);
 }
 
+template <bool TAIL>
 int launch_dma32(const GemmArgs &g, const GemmParams &p, void *stream) {
     constexpr size_t lds = size_t(2) * kD32Stage + size_t(256) * sizeof(int64_t);
     static_assert(lds <= kLdsPerCu, "LDS of one workgroup");
-    auto kern = gemm_dma32_kernel;
+    auto kern = gemm_dma32_kernel<TAIL>;
     if (!launch_check_mode()) {
         static const int set = int(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
@@ -1473,12 +1543,13 @@ int launch_dma32(const GemmArgs &g, const GemmParams &p, void *stream) {
     return launch_status();
 }
 
-template <bool OB, bool MN, int BN = 256, bool FP8 = false>
+template <bool OB, bool MN, int BN = 256, bool FP8 = false, bool TAIL = false>
 int launch_dma(const GemmArgs &g, const GemmParams &p, void *stream) {
     static_assert(!MN || (BN == 256 && !FP8), "the dW tile is 256 wide, bf16");
+    static_assert(MN || !TAIL, "whole stages");
     constexpr size_t lds = MN ? 0 : dma_main_lds<OB>() + size_t(512) * sizeof(int64_t);
     static_assert(lds <= kLdsPerCu, "LDS of one workgroup");
-    auto kern = MN ? gemm_dma_mn_kernel<OB> : gemm_dma_kernel<OB, BN, FP8>;
+    auto kern = MN ? gemm_dma_mn_kernel<OB, TAIL> : gemm_dma_kernel<OB, BN, FP8>;
     if (!MN && !launch_check_mode()) {
         static const int set = int(hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
@@ -1708,10 +1779,10 @@ bool fast_ok_k(const GemmArgs &g, int64_t kchunk, int ktb) {
     return g.K % kt == 0 && kchunk % kt == 0;
 }
 
-bool fast_ok(const GemmArgs &g, int64_t kchunk, int ktb) {
+bool fast_ok(const GemmArgs &g, int64_t kchunk, int ktb, bool tail_ok = false) {
     const int64_t sz = g.dtype == COMERA_BF16 ? 2 : (g.dtype == kDtypeFp8 ? 1 : 4);
     const int64_t kt = ktb / sz;
-    if (g.K % kt || kchunk % kt) return false;
+    if ((!tail_ok && g.K % kt) || kchunk % kt) return false;
     auto op_ok = [&](const void *ptr, int64_t ld, bool kc, int64_t R) {
         if (reinterpret_cast<uintptr_t>(ptr) % 16 || (ld * sz) % 16) return false;
         if (kc) return R * ld * sz < (int64_t(1) << 32);
@@ -1815,7 +1886,10 @@ int launch_gemm(const GemmArgs &g, void *stream) {
 
         const int64_t kt = ktb / esz;
         pf.kchunk = ceil_div(p.kchunk, kt) * kt;
-        if (!fast_ok(gg, pf.kchunk, ktb)) {
+        // the straight-to-LDS kernels of M/N-contiguous operands (dW) take a
+        // K that ends within a stage
+        const bool tail_ok = !g.a_kc && !g.b_kc && (fast == F256x256_dma || fast == F128x128_dma32);
+        if (!fast_ok(gg, pf.kchunk, ktb, tail_ok)) {
             // a K that is a multiple of the 64-byte K row but not of the
             // 128-byte one keeps a fast 128 x 128 tile on 64-byte rows
             const bool was32 = fast == F128x128_dma32;
@@ -1843,7 +1917,8 @@ int launch_gemm(const GemmArgs &g, void *stream) {
         if (!pers_ok(gg)) return int(hipErrorInvalidValue);
         return g.dtype == kDtypeFp8 ? launch_dma_pers<true>(gg, pf, stream) : launch_dma_pers<false>(gg, pf, stream);
     }
-    if (fast == F128x128_dma32) return launch_dma32(gg, pf, stream);
+    if (fast == F128x128_dma32)
+        return g.K % kD32KT ? launch_dma32<true>(gg, pf, stream) : launch_dma32<false>(gg, pf, stream);
     if (fast == F256x192_dma) {
         if (g.dtype != COMERA_BF16 || !g.a_kc || !g.b_kc) return int(hipErrorInvalidValue);
         return g.out_bf16 ? launch_dma<true, false, 192>(gg, pf, stream) : launch_dma<false, false, 192>(gg, pf, stream);
@@ -1856,6 +1931,9 @@ int launch_gemm(const GemmArgs &g, void *stream) {
     if (fast == F256x256_dma) {
         if (g.dtype != COMERA_BF16 || g.a_kc != g.b_kc) return int(hipErrorInvalidValue);
         if (g.a_kc) return g.out_bf16 ? launch_dma<true, false>(gg, pf, stream) : launch_dma<false, false>(gg, pf, stream);
+        if (g.K % kDmaKT)
+            return g.out_bf16 ? launch_dma<true, true, 256, false, true>(gg, pf, stream)
+                              : launch_dma<false, true, 256, false, true>(gg, pf, stream);
         return g.out_bf16 ? launch_dma<true, true>(gg, pf, stream) : launch_dma<false, true>(gg, pf, stream);
     }
     if (g.dtype == kDtypeFp8) {
