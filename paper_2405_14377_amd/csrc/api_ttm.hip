@@ -287,54 +287,37 @@ int project_cores(const comera_ttm_plan_s *sp, const DenseBuild &bd, const float
 
 // The expand kernel sums the partials of each core in a fixed order,
 // unfolds the compacted layout, applies the masks and writes zeros on
-// inactive slices.
-int expand_cores(const comera_ttm_plan_s *p, const float *const *part, const int *nsplit, const CoreStrides *st,
-                 const float *const *D, float *const *dG, void *stream) {
+// inactive slices; the mask gradients read the sums it leaves behind.
+int core_grads(const comera_ttm_plan_s *p, const float *const *part, const int *nsplit, const CoreStrides *st,
+               const float *const *G, const float *const *D, float *const *dG, float *const *dD, void *stream) {
+    if (!dG && !dD) return 0;
     const int d = p->d;
     ExpandArgs xa;
-    std::memset(&xa, 0, sizeof(xa));
-    xa.d = d;
-    xa.compacted = p->compacted ? 1 : 0;
-    for (int k = 0; k < d; ++k) {
-        xa.part[k] = part[k];
-        xa.splits[k] = nsplit[k];
-        xa.st[k] = st[k];
-        xa.D[k] = (D && k < d - 1) ? D[k] : nullptr;
-        xa.dG[k] = dG[k];
-        xa.m[k] = int(p->s.m[k]);
-        xa.n[k] = int(p->s.n[k]);
-    }
-    for (int k = 0; k <= d; ++k) {
-        xa.r[k] = int(p->s.r[k]);
-        xa.rc[k] = int(p->rho[k]);
-        xa.act[k] = p->act[k];
-    }
-    return note_hip(launch_expand(xa, stream), "expand");
-}
-
-int mask_grads(const comera_ttm_plan_s *p, const float *const *part, const int *nsplit, const CoreStrides *st,
-               const float *const *G, float *const *dD, void *stream) {
-    if (!dD) return 0;
-    const int d = p->d;
     MaskGradArgs ma;
+    std::memset(&xa, 0, sizeof(xa));
     std::memset(&ma, 0, sizeof(ma));
-    ma.d = d;
-    ma.compacted = p->compacted ? 1 : 0;
+    xa.d = ma.d = d;
+    xa.compacted = ma.compacted = p->compacted ? 1 : 0;
     for (int k = 0; k < d; ++k) {
-        ma.part[k] = part[k];
-        ma.splits[k] = nsplit[k];
-        ma.st[k] = st[k];
+        ma.dD[k] = dD && k < d - 1 ? dD[k] : nullptr;
+        xa.part[k] = part[k];
+        xa.keep[k] = ma.dD[k] ? const_cast<float *>(part[k]) : nullptr;
+        xa.splits[k] = nsplit[k];
+        xa.D[k] = (D && k < d - 1) ? D[k] : nullptr;
+        xa.dG[k] = dG ? dG[k] : nullptr;
+        ma.sum[k] = part[k];
         ma.G[k] = G[k];
-        ma.dD[k] = k < d - 1 ? dD[k] : nullptr;
-        ma.m[k] = int(p->s.m[k]);
-        ma.n[k] = int(p->s.n[k]);
+        xa.st[k] = ma.st[k] = st[k];
+        xa.m[k] = ma.m[k] = int(p->s.m[k]);
+        xa.n[k] = ma.n[k] = int(p->s.n[k]);
     }
     for (int k = 0; k <= d; ++k) {
-        ma.r[k] = int(p->s.r[k]);
-        ma.rc[k] = int(p->rho[k]);
-        ma.act[k] = p->act[k];
+        xa.r[k] = ma.r[k] = int(p->s.r[k]);
+        xa.rc[k] = ma.rc[k] = int(p->rho[k]);
+        xa.act[k] = ma.act[k] = p->act[k];
     }
-    return note_hip(launch_mask_grad(ma, stream), "mask gradients");
+    if (int e = launch_expand(xa, stream)) return note_hip(e, "expand");
+    return dD ? note_hip(launch_mask_grad(ma, stream), "mask gradients") : 0;
 }
 
 }  // namespace comera
@@ -763,8 +746,7 @@ comera_status backward_impl(comera_ttm_plan_t p, int64_t b, const void *X, const
     if (e) return COMERA_ERR_HIP;
     CoreStrides st[kMaxCores];
     dense_strides(p, st);
-    if (want_dg && expand_cores(p, part, nsplit, st, D, dG, stream)) return COMERA_ERR_HIP;
-    return mask_grads(p, part, nsplit, st, G, dD, stream) ? COMERA_ERR_HIP : COMERA_OK;
+    return core_grads(p, part, nsplit, st, G, D, want_dg ? dG : nullptr, dD, stream) ? COMERA_ERR_HIP : COMERA_OK;
 }
 
 }  // namespace

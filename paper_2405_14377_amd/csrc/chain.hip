@@ -642,8 +642,7 @@ comera_status chain_backward(const comera_ttm_plan_s *p, int64_t b, const void *
         nsplit[k] = grid;
         st[k] = core_strides(a.rc[k], a.m[k], a.n[k], a.rc[k + 1], false);
     }
-    if (dG && expand_cores(p, part, nsplit, st, D, dG, stream)) return COMERA_ERR_HIP;
-    return mask_grads(p, part, nsplit, st, G, dD, stream) ? COMERA_ERR_HIP : COMERA_OK;
+    return core_grads(p, part, nsplit, st, G, D, dG, dD, stream) ? COMERA_ERR_HIP : COMERA_OK;
 }
 
 }  // namespace comera

@@ -228,6 +228,7 @@ int launch_fold(const FoldArgs &a, void *stream);
 
 struct ExpandArgs {
     const float *part[kMaxCores];   // [splits][compacted core placed by st[k]]
+    float *keep[kMaxCores];         // null, or part[k]: its first partial receives the sum of all
     const float *D[kMaxCores];
     float *dG[kMaxCores];
     BondBits act[kMaxCores + 1];
@@ -245,11 +246,9 @@ struct ExpandArgs {
 int launch_expand(const ExpandArgs &a, void *stream);
 
 // dD_k (k = 0..d-2, r_{k+1} floats each, null = skip) from the compacted
-// split partials of the masked-core gradients (as for expand) and the raw
-// cores G_k
+// masked-core gradients (the sums that expand kept) and the raw cores G_k
 struct MaskGradArgs {
-    const float *part[kMaxCores];
-    int splits[kMaxCores];
+    const float *sum[kMaxCores];
     CoreStrides st[kMaxCores];
     const float *G[kMaxCores];
     float *dD[kMaxCores];
@@ -503,12 +502,12 @@ int dw_gemm(const comera_ttm_plan_s *sp, const void *A, int64_t lda, const void 
 // partials of dW; want[k] false skips core k
 int project_cores(const comera_ttm_plan_s *sp, const DenseBuild &bd, const float *dwp, int splits,
                   const bool *want, void *ws, const float **part, int *nsplit, void *stream);
-// sum the partials of every core of layer p, unfold and apply the masks
-int expand_cores(const comera_ttm_plan_s *p, const float *const *part, const int *nsplit, const CoreStrides *st,
-                 const float *const *D, float *const *dG, void *stream);
-// mask gradients dD_k of layer p from the same partials (dD null: nothing)
-int mask_grads(const comera_ttm_plan_s *p, const float *const *part, const int *nsplit, const CoreStrides *st,
-               const float *const *G, float *const *dD, void *stream);
+// core gradients dG_k (null or entries null: not written) and mask gradients
+// dD_k (likewise) of layer p: the partials of every core (workspace memory,
+// changed by the call) summed, unfolded and masked, and contracted with the
+// raw cores
+int core_grads(const comera_ttm_plan_s *p, const float *const *part, const int *nsplit, const CoreStrides *st,
+               const float *const *G, const float *const *D, float *const *dG, float *const *dD, void *stream);
 // out[t][j][i] = in[t][i][j] for t < b, i < M, j < T (elements of esz bytes)
 int launch_permute_tokens(const void *in, void *out, int64_t b, int64_t M, int64_t T, int esz, void *stream);
 

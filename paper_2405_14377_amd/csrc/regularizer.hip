@@ -8,10 +8,12 @@
 // else s_k ||D_{k-1}||_1, and core k+1's term, s_{k+1} for the last core
 // else s_{k+1} ||D_{k+1}||_1.  sign(0) = 0.
 //
-// Two small launches: a grid-stride update of every core gradient, and one
-// workgroup that forms the l1 norms of the masks in a fixed order (thread t
-// sums entries t, t + 256, ... then a fixed tree) and updates dD, so the
-// result is bitwise reproducible.
+// One launch: a grid-stride update of every core gradient (grid row k), and
+// one more grid row whose first workgroup forms the l1 norms of the masks in
+// a fixed order (thread t sums entries t, t + 256, ... then a fixed tree) and
+// updates dD, so the result is bitwise reproducible.  Bound by launch
+// latency: the two parts were two launches of 5 us each on the 3072 -> 768
+// layer.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -34,10 +36,10 @@ struct RegArgs {
     float *dG[kMax];
     float *dD[kMax];
     float two_beta, gamma;
+    int core_rows;             // grid rows of the core terms; the row after them is the masks'
 };
 
-__global__ __launch_bounds__(256) void reg_core_kernel(RegArgs a) {
-    const int k = blockIdx.y;
+__device__ __forceinline__ void core_terms(const RegArgs &a, int k) {
     float *out = a.dG[k];
     if (!out) return;
     const float *G = a.G[k];
@@ -46,7 +48,7 @@ __global__ __launch_bounds__(256) void reg_core_kernel(RegArgs a) {
         out[i] = out[i] + a.two_beta * G[i];
 }
 
-__global__ __launch_bounds__(256) void reg_mask_kernel(RegArgs a) {
+__device__ __forceinline__ void mask_terms(const RegArgs &a) {
     __shared__ float red[256];
     __shared__ float norm[kMax];
     const int t = threadIdx.x;
@@ -75,6 +77,13 @@ __global__ __launch_bounds__(256) void reg_mask_kernel(RegArgs a) {
             out[c] = out[c] + sg * coef;
         }
     }
+}
+
+__global__ __launch_bounds__(256) void reg_core_kernel(RegArgs a) {
+    if (int(blockIdx.y) < a.core_rows)
+        core_terms(a, blockIdx.y);
+    else if (blockIdx.x == 0)
+        mask_terms(a);
 }
 
 }  // namespace
@@ -112,14 +121,10 @@ extern "C" comera_status comera_ttm_regularizer_grads(const comera_ttm_shape *s,
         for (int k = 0; k + 1 < s->d; ++k)
             if (!a.D[k]) return COMERA_ERR_INVALID_ARG;
     hipStream_t st = hipStream_t(stream);
-    if (mx > 0) {
-        const unsigned gx = unsigned(std::min<int64_t>((mx + 255) / 256, 1024));
-        COMERA_LAUNCH(reg_core_kernel, dim3(gx, unsigned(s->d)), dim3(256), 0, st, a);
-        if (comera::note_hip(comera::launch_status(), "regulariser: core terms")) return COMERA_ERR_HIP;
-    }
-    if (any_dD) {
-        COMERA_LAUNCH(reg_mask_kernel, dim3(1), dim3(256), 0, st, a);
-        if (comera::note_hip(comera::launch_status(), "regulariser: mask terms")) return COMERA_ERR_HIP;
-    }
-    return COMERA_OK;
+    a.core_rows = mx > 0 ? s->d : 0;
+    const int rows = a.core_rows + (any_dD ? 1 : 0);
+    if (rows == 0) return COMERA_OK;
+    const unsigned gx = unsigned(std::max<int64_t>(1, std::min<int64_t>((mx + 255) / 256, 1024)));
+    COMERA_LAUNCH(reg_core_kernel, dim3(gx, unsigned(rows)), dim3(256), 0, st, a);
+    return comera::note_hip(comera::launch_status(), "regulariser") ? COMERA_ERR_HIP : COMERA_OK;
 }

@@ -277,8 +277,7 @@ comera_status sweep_backward(const comera_ttm_plan_s *p, int64_t b, const void *
             return status_of(e);
     }
     timing_end(const_cast<comera_ttm_plan_s *>(p), COMERA_KERNEL_DW, stream, ev);
-    if (dG && expand_cores(p, part, nsplit, L.st, D, dG, stream)) return COMERA_ERR_HIP;
-    return status_of(mask_grads(p, part, nsplit, L.st, G, dD, stream));
+    return status_of(core_grads(p, part, nsplit, L.st, G, D, dG, dD, stream));
 }
 
 }  // namespace comera

@@ -105,7 +105,7 @@ __global__ __launch_bounds__(NT) void expand_kernel(ExpandArgs a) {
     __shared__ float red[NT + kExpandMaxGroups];   // [G][no + 1]
     int k = 0;
     while (k + 1 < a.d && int(blockIdx.x) >= a.blk0[k + 1]) ++k;
-    if (!a.dG[k]) return;
+    if (!a.dG[k] && !a.keep[k]) return;
     const int G = a.groups[k], no = NT / G;
     const int rl = a.r[k], rr = a.r[k + 1], m = a.m[k], n = a.n[k];
     const int crl = a.rc[k], crr = a.rc[k + 1];
@@ -153,20 +153,28 @@ __global__ __launch_bounds__(NT) void expand_kernel(ExpandArgs a) {
         float t = red[lo];
         for (int gg = 1; gg < G; ++gg) t += red[gg * (no + 1) + lo];
         if (ci < 0) t = 0.f;
-        else if (D) t *= D[o % rr];
-        a.dG[k][o] = t;
+        // the sum stays in the first partial (only this workgroup reads or
+        // writes entry ci of core k) for the mask gradients
+        else if (a.keep[k]) a.keep[k][ci] = t;
+        if (a.dG[k]) a.dG[k][o] = (ci >= 0 && D) ? t * D[o % rr] : t;
     }
 }
 
 // Mask gradients (chain rule through eq. Wcompress): with dG~_k the gradient
-// of the masked core G~_k = G_k D_k (the sum of the compacted partials),
+// of the masked core G~_k = G_k D_k (the sum of its compacted partials, which
+// the expand launch before this one left in the first partial),
 //   dD_k[c] = sum_{a, m, n} dG~_k[a, m, n, c] G_k[a, m, n, c].
-// One workgroup per (bond k, entry c): thread t sums the elements t, t + 256,
-// ... in that order (each from its split partials in split order), then a
-// fixed-shape tree adds the 256 thread sums, so the result is bitwise
-// reproducible.  Entries dropped by the compaction (declared inactive) get 0.
-__global__ __launch_bounds__(256) void mask_grad_kernel(MaskGradArgs a) {
-    __shared__ float red[256];
+// One workgroup per (bond k, entry c): thread t sums the elements t, t + 1024,
+// ... in that order, then a fixed-shape tree adds the thread sums, so the
+// result is bitwise reproducible.  Entries dropped by the compaction
+// (declared inactive) get 0.  Bound by the latency of its loads (a few
+// kilobytes per workgroup): four elements' loads are in flight per thread,
+// which is all of them on the layers here.  Summing the partials here too, by
+// 256 threads, took 43 us on the 3072 -> 768 layer (r = 30); 9 us now.
+constexpr int kMaskGradInFlight = 4, kMaskGradThreads = 1024;
+__global__ __launch_bounds__(kMaskGradThreads) void mask_grad_kernel(MaskGradArgs a) {
+    __shared__ float red[kMaskGradThreads / 64];
+    __shared__ int map_l[256];   // compacted entry of each left-bond entry, -1 = inactive
     int k = 0;
     while (k + 1 < a.d - 1 && int(blockIdx.x) >= a.blk0[k + 1]) ++k;
     float *out = a.dD[k];
@@ -178,30 +186,44 @@ __global__ __launch_bounds__(256) void mask_grad_kernel(MaskGradArgs a) {
         if (threadIdx.x == 0) out[c] = 0.f;
         return;
     }
-    const int64_t csize = int64_t(a.rc[k]) * m * n * a.rc[k + 1];
-    const CoreStrides st = a.st[k];
-    const float *part = a.part[k];
-    const float *G = a.G[k];
-    const int S = a.splits[k];
-    const int mn_ = m * n;
-    float v = 0.f;
-    for (int e = threadIdx.x; e < rl * mn_; e += 256) {
-        const int al = e / mn_, mn = e - al * mn_;
-        const int ca = (a.compacted && k > 0) ? rank_bit(a.act[k], al) : al;
-        if (ca < 0) continue;   // inactive left slice: G~_{k-1} is zero there, so is dG~_k
-        const int jm = mn / n, in = mn - jm * n;
-        const int64_t ci = int64_t(ca) * st.sa + jm * st.sm + in * st.sn + int64_t(cc) * st.sc;
-        float g = 0.f;
-        for (int s = 0; s < S; ++s) g += part[s * csize + ci];
-        v += g * G[int64_t(e) * rr + c];
-    }
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
+    const bool mapped = a.compacted && k > 0;   // then every rank is at most 256
+    if (mapped) {
+        if (threadIdx.x < 256) map_l[threadIdx.x] = rank_bit(a.act[k], threadIdx.x);
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[c] = red[0];
+    const CoreStrides st = a.st[k];
+    const float *__restrict__ g = a.sum[k];
+    const float *__restrict__ G = a.G[k];
+    const int mn_ = m * n, total = rl * mn_;
+    float v = 0.f;
+    for (int e0 = threadIdx.x; e0 < total; e0 += kMaskGradThreads * kMaskGradInFlight) {
+        float x[kMaskGradInFlight], y[kMaskGradInFlight];
+#pragma unroll
+        for (int u = 0; u < kMaskGradInFlight; ++u) {
+            const int e = e0 + kMaskGradThreads * u;
+            x[u] = 0.f;
+            y[u] = 0.f;
+            if (e < total) {
+                const int al = e / mn_, mn = e - al * mn_;
+                const int ca = mapped ? map_l[al] : al;
+                if (ca >= 0) {   // inactive left slice: G~_{k-1} is zero there, so is dG~_k
+                    const int jm = mn / n, in = mn - jm * n;
+                    x[u] = g[int64_t(ca) * st.sa + jm * st.sm + in * st.sn + int64_t(cc) * st.sc];
+                    y[u] = G[int64_t(e) * rr + c];
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kMaskGradInFlight; ++u) v += x[u] * y[u];
+    }
+    for (int w = 32; w > 0; w >>= 1) v += __shfl_down(v, w);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float t = red[0];
+        for (int w = 1; w < kMaskGradThreads / 64; ++w) t += red[w];
+        out[c] = t;
+    }
 }
 
 // sum of the split partials in split order, eight loads in flight
@@ -313,13 +335,13 @@ int launch_expand(const ExpandArgs &a_in, void *stream) {
         int G = 1;
         while (G < gcap && G * 8 < a.splits[k]) G *= 2;
         a.groups[k] = G;
-        if (a.dG[k]) gmax = std::max(gmax, G);
+        if (a.dG[k] || a.keep[k]) gmax = std::max(gmax, G);
     }
     const int nt = gmax <= 8 ? 256 : 1024;
     int blocks = 0;
     for (int k = 0; k < a.d; ++k) {
         a.blk0[k] = blocks;
-        const int64_t total = a.dG[k] ? int64_t(a.r[k]) * a.m[k] * a.n[k] * a.r[k + 1] : 0;
+        const int64_t total = a.dG[k] || a.keep[k] ? int64_t(a.r[k]) * a.m[k] * a.n[k] * a.r[k + 1] : 0;
         const int no = nt / a.groups[k];
         blocks += int((total + no - 1) / no);
     }
@@ -341,7 +363,7 @@ int launch_mask_grad(const MaskGradArgs &a_in, void *stream) {
     }
     for (int k = std::max(0, a.d - 1); k < kMaxCores; ++k) a.blk0[k] = blocks;
     if (blocks == 0) return 0;
-    COMERA_LAUNCH(mask_grad_kernel, dim3(unsigned(blocks)), dim3(256), 0, hipStream_t(stream), a);
+    COMERA_LAUNCH(mask_grad_kernel, dim3(unsigned(blocks)), dim3(kMaskGradThreads), 0, hipStream_t(stream), a);
     return launch_status();
 }
 
