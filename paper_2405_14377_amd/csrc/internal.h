@@ -100,6 +100,21 @@ constexpr int kScW = 0, kScX = 1, kScDY = 2, kScFwd = 3, kScDX = 4, kScDW = 5;
 //   left to right, dY state H_g (input of step g): [(b, M_<g, N_>g)][(M_g, ae_g)]
 // so the gradient of W'_g is one product A^T B of the two states that meet
 // at group g, with the token-like index (b and the outer factors) as K.
+// Workspace of the two-group sweep through one bond (bottleneck.hip): chain
+// data of each group (index: group, chain position), the operands of the
+// batch products (op [N][RP], opt in 64-byte pieces of its columns), the states of X
+// (s) and dY (t), the split partials of dA and dB^T and their sum, and the
+// masked-core gradients for the mask gradients.
+struct BottleneckLayout {
+    bool on = false;
+    int R = 0, RP = 0;                 // rank of the bond; the same padded (32 or 64)
+    int64_t spitch = 0;                // tokens per row of a bf16 state
+    int64_t kchunk = 0;                // tokens per split of the meets
+    size_t v[2][kMaxCores + 1] = {}, c[2][kMaxCores + 1] = {};
+    size_t op[2] = {}, opt[2] = {}, s = 0, t = 0, part = 0, sum = 0;
+    size_t keep[kMaxCores] = {};
+    size_t total = 0;
+};
 struct SweepLayout {
     int G = 0;
     int dir = 0;                       // COMERA_ORDER_SWEEP_RL or _LR
@@ -114,6 +129,7 @@ struct SweepLayout {
     int64_t part_elems = 0;
     CoreStrides st[kMaxCores];         // placement of each folded core in its group
     size_t total = 0;
+    BottleneckLayout bn;               // when bn.on, the sweep runs on it and needs nothing above
 };
 
 }  // namespace comera
@@ -523,6 +539,15 @@ comera_status chain_forward(const comera_ttm_plan_s *p, int64_t b, const void *X
 comera_status chain_backward(const comera_ttm_plan_s *p, int64_t b, const void *X, const void *dY,
                              const float *const *G, const float *const *D, void *dX, float *const *dG,
                              float *const *dD, void *ws, void *stream);
+
+// the two-group sweep through one bond (bottleneck.hip); layout_bottleneck is
+// false when the sweep L is of another kind or outside the kernels' limits
+bool layout_bottleneck(const comera_ttm_plan_s *p, const SweepLayout &L, size_t cap, BottleneckLayout &B);
+comera_status bottleneck_forward(const comera_ttm_plan_s *p, int64_t b, const void *X, const float *const *G,
+                                 const float *const *D, void *Y, void *ws, void *stream);
+comera_status bottleneck_backward(const comera_ttm_plan_s *p, int64_t b, const void *X, const void *dY,
+                                  const float *const *G, const float *const *D, void *dX, float *const *dG,
+                                  float *const *dD, void *ws, void *stream);
 
 // sweep orders (sweep.hip)
 comera_status sweep_forward(const comera_ttm_plan_s *p, int64_t b, const void *X, const float *const *G,

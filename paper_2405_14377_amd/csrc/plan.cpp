@@ -463,6 +463,10 @@ bool layout_sweep(const comera_ttm_plan_s *p, int kind, uint32_t cuts, SweepLayo
         for (int h = lo; h < hi; ++h) x *= double(v[h]);
         return x;
     };
+    if (layout_bottleneck(p, L, size_t(kSweepCap), L.bn)) {
+        L.total = L.bn.total;
+        return true;
+    }
     const double b = double(std::max<int64_t>(p->batch, 1));
     const size_t esz = p->s.act == COMERA_BF16 ? 2 : 4;
     double off = 0;

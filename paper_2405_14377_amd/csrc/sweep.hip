@@ -154,6 +154,7 @@ int sweep_x(const comera_ttm_plan_s *p, int64_t b, const void *X0, void *Y, void
 comera_status sweep_forward(const comera_ttm_plan_s *p, int64_t b, const void *X, const float *const *G,
                             const float *const *D, void *Y, void *ws, void *stream) {
     const SweepLayout &L = p->sweep;
+    if (L.bn.on) return bottleneck_forward(p, b, X, G, D, Y, ws, stream);
     const int esz = p->s.act == COMERA_BF16 ? 2 : 4;
     Groups gr;
     if (int e = build_groups(p, G, D, ws, gr, stream)) return status_of(e);
@@ -174,6 +175,7 @@ comera_status sweep_backward(const comera_ttm_plan_s *p, int64_t b, const void *
                              const float *const *G, const float *const *D, void *dX, float *const *dG,
                              float *const *dD, void *ws, void *stream) {
     const SweepLayout &L = p->sweep;
+    if (L.bn.on) return bottleneck_backward(p, b, X, dY, G, D, dX, dG, dD, ws, stream);
     const int NG = L.G;
     const int d = p->d;
     const int esz = p->s.act == COMERA_BF16 ? 2 : 4;
