@@ -34,6 +34,12 @@ constexpr int kSub = kBlk / 256;
 constexpr int kGlVp = 4;            // prefixes per dG_last workgroup (= partial)
 constexpr size_t kEmbLds = 64 * 1024;
 
+// v where mask is ~0, +0 where it is 0.  The operand loads below run at clamped
+// indices and are masked: a select would be compiled into a branch around each
+// load, and every load would wait for its own round trip.
+__device__ __forceinline__ float masked(float v, uint32_t mask) { return __uint_as_float(__float_as_uint(v) & mask); }
+__device__ __forceinline__ uint32_t mask_if(bool b) { return b ? ~0u : 0u; }
+
 __device__ __forceinline__ uint64_t lanemask_lt() {
     const int lane = threadIdx.x & 63;
     return lane ? ((~0ull) >> (64 - lane)) : 0ull;
@@ -177,12 +183,12 @@ __global__ __launch_bounds__(256) void embed_rows_mfma_kernel(const int64_t *__r
     const float *ar = Apre ? Apre + int64_t(vp) * Ep * R : nullptr;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        const int a = 4 * s + q;
-        const bool ok = a < R;
+        const int a = 4 * s + q, ac = min(a, R - 1);
+        const uint32_t ma = mask_if(a < R);
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt)
-            av[tt][s] = ok ? (ar ? ar[int64_t(16 * tt + r) * sE + int64_t(a) * sR] : 1.f) : 0.f;
-        bv[s] = (ok && r < Es) ? Gs[(int64_t(a) * Vs + vs) * Es + r] : 0.f;
+            av[tt][s] = masked(ar ? ar[(16 * tt + r) * sE + ac * sR] : 1.f, ma);
+        bv[s] = masked(Gs[(int64_t(ac) * Vs + vs) * Es + min(r, Es - 1)], ma & mask_if(r < Es));
     }
     f32x4 acc[NT];
 #pragma unroll
@@ -307,7 +313,7 @@ __device__ __forceinline__ uint32_t key_of(const int64_t *ids, int i, int64_t V)
 // headpos[0 .. nclear) to -1 and zero[0 .. nzero) to 0.0f.
 __global__ __launch_bounds__(256) void radix_hist_kernel(const int64_t *__restrict__ ids, const uint32_t *kin, int n,
                                                          int64_t V, int shift, int nblk, int *__restrict__ hist,
-                                                         int *__restrict__ bad_out, int *err_flag,
+                                                         int by_block, int *__restrict__ bad_out, int *err_flag,
                                                          int *__restrict__ headpos, int64_t nclear,
                                                          float *__restrict__ zero, int64_t nzero) {
     __shared__ int h[256];
@@ -334,7 +340,7 @@ __global__ __launch_bounds__(256) void radix_hist_kernel(const int64_t *__restri
     }
     if (bad) atomicAdd(&bad_s, bad);
     __syncthreads();
-    hist[threadIdx.x * nblk + b] = h[threadIdx.x];
+    hist[by_block ? b * 256 + threadIdx.x : threadIdx.x * nblk + b] = h[threadIdx.x];
     if (threadIdx.x == 0 && bad_out) {
         bad_out[b] = bad_s;
         if (bad_s && err_flag) *err_flag = 1;
@@ -383,7 +389,7 @@ __global__ __launch_bounds__(1024) void radix_scan_kernel(int *hist, int nblk, c
 }
 
 // With scan != 0 (few blocks) the workgroup derives its own digit offsets
-// from the raw histograms: offs[dg][b] = sum of all counts of digits below
+// from the raw histograms ([block][digit]): offs[dg][b] = sum of all counts of digits below
 // dg plus the counts of digit dg in blocks below b (and block 0 writes
 // meta[0] = n - out-of-range ids when bad != null), so no scan kernel runs.
 __global__ __launch_bounds__(256) void radix_scatter_kernel(const int64_t *__restrict__ ids, const uint32_t *kin,
@@ -398,11 +404,19 @@ __global__ __launch_bounds__(256) void radix_scatter_kernel(const int64_t *__res
     const int b = blockIdx.x;
     if (scan) {
         // thread tid = digit: its total and its count in the blocks below b
+        // (histograms by block: consecutive threads read consecutive counts,
+        // sixteen rounds in flight; digit by digit they cost 8 us per pass on
+        // 49 blocks)
         int tot = 0, below = 0;
-        for (int bb = 0; bb < nblk; ++bb) {
-            const int h = offs[tid * nblk + bb];
-            tot += h;
-            below += bb < b ? h : 0;
+        for (int b0 = 0; b0 < nblk; b0 += 16) {
+            int h[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) h[u] = b0 + u < nblk ? offs[(b0 + u) * 256 + tid] : 0;
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                tot += h[u];
+                below += b0 + u < b ? h[u] : 0;
+            }
         }
         // exclusive scan of the digit totals (wave scans, then the four waves)
         const int lane = tid & 63;
@@ -559,15 +573,43 @@ __global__ __launch_bounds__(256) void embed_segsum_kernel(const float *__restri
 }
 
 // A segment that starts in chunk c and runs past its end: S[head] =
-// Plast[c] + Pfirst[c+1] + ... + Pfirst[cend-1].  Workgroup (c, column
-// block) of 64 columns x 4 groups: group g sums a fixed quarter of that list
-// in order (eight loads in flight), then the quarters are added in order.
+// Plast[c] + Pfirst[c+1] + ... + Pfirst[cend-1].  Workgroup (c, block of 64
+// column vectors) x 4 groups: group g sums a fixed quarter of that list in
+// order (eight loads in flight), then the quarters are added in order.  A
+// vector is four columns where rows are 16-byte aligned: most chunks have
+// nothing to do, and a workgroup per 64 columns of each cost 26 us on 50001
+// ids of 768 columns, 10 us now.
+template <typename V>
+__device__ __forceinline__ void fix_columns(int cols, int c, int head, int cnt, const float *Pfirst,
+                                            const float *Plast, float *S, V (*red)[64]) {
+    const int g = threadIdx.x >> 6, lc = threadIdx.x & 63;
+    const int i0 = int(int64_t(g) * cnt / 4), i1 = int(int64_t(g + 1) * cnt / 4);
+    const V *pf = reinterpret_cast<const V *>(Pfirst), *pl = reinterpret_cast<const V *>(Plast);
+    const int col = blockIdx.y * 64 + lc, colc = min(col, cols - 1);
+    V acc{};
+    for (int i = i0; i < i1; i += 8) {
+        V x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int ii = min(i + u, i1 - 1);
+            x[u] = (ii == 0 ? pl + int64_t(c) * cols : pf + int64_t(c + ii) * cols)[colc];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (i + u < i1) acc += x[u];
+    }
+    red[g][lc] = acc;
+    __syncthreads();
+    if (g == 0 && col < cols)
+        reinterpret_cast<V *>(S)[int64_t(head) * cols + col] = ((red[0][lc] + red[1][lc]) + red[2][lc]) + red[3][lc];
+}
+
 __global__ __launch_bounds__(256) void embed_segfix_kernel(int E, const int *__restrict__ meta,
                                                            const uint32_t *__restrict__ keys,
                                                            const float *__restrict__ Pfirst,
                                                            const float *__restrict__ Plast, float *__restrict__ S) {
     __shared__ int info[2];
-    __shared__ float red[4][64];
+    __shared__ f32x4 red[4][64];
     const int nv = meta[0];
     const int c = blockIdx.x;
     const int p0 = c * kEmbedItem, p1 = min(nv, p0 + kEmbedItem);
@@ -586,25 +628,10 @@ __global__ __launch_bounds__(256) void embed_segfix_kernel(int E, const int *__r
     const int head = info[0];
     if (head < 0) return;
     const int cnt = info[1] - c;           // Plast[c] then Pfirst[c+1 .. cend-1]
-    const int g = threadIdx.x >> 6, lc = threadIdx.x & 63;
-    const int col = blockIdx.y * 64 + lc;
-    const int colc = min(col, E - 1);
-    const int i0 = int(int64_t(g) * cnt / 4), i1 = int(int64_t(g + 1) * cnt / 4);
-    float acc = 0.f;
-    for (int i = i0; i < i1; i += 8) {
-        float x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int ii = min(i + u, i1 - 1);
-            x[u] = ii == 0 ? Plast[int64_t(c) * E + colc] : Pfirst[int64_t(c + ii) * E + colc];
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (i + u < i1) acc += x[u];
-    }
-    red[g][lc] = acc;
-    __syncthreads();
-    if (g == 0 && col < E) S[int64_t(head) * E + col] = ((red[0][lc] + red[1][lc]) + red[2][lc]) + red[3][lc];
+    if ((E & 3) == 0)
+        fix_columns<f32x4>(E / 4, c, head, cnt, Pfirst, Plast, S, red);
+    else
+        fix_columns<float>(E, c, head, cnt, Pfirst, Plast, S, reinterpret_cast<float(*)[64]>(red));
 }
 
 // ---------------------------------------------------------------- per prefix
@@ -859,28 +886,44 @@ __global__ __launch_bounds__(256) void embed_dapre_mfma_kernel(const int *__rest
     for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int c = 0; c < 2; ++c) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int u = u0; u < u1; ++u) {
+    // the next id's operands load while the current ones are multiplied
+    float sa[2][NT][NKS], gb[2][2][NKS];
+    // (masked when they are used: masking waits for the load)
+    auto load = [&](int u, float (&x)[NT][NKS], float (&y)[2][NKS]) {
         const int vs = vsl[u];
         const float *su = S + int64_t(hpl[u]) * E;
-        float sa[NT][NKS], gb[2][NKS];
 #pragma unroll
         for (int k = 0; k < NKS; ++k) {
-            const int es = NKS * q + k;
+            const int ec = min(NKS * q + k, Es - 1);
 #pragma unroll
-            for (int t = 0; t < NT; ++t) sa[t][k] = es < Es ? su[(16 * t + r) * Es + es] : 0.f;
+            for (int t = 0; t < NT; ++t) x[t][k] = su[(16 * t + r) * Es + ec];
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const int a = 16 * c + r;
-                gb[c][k] = (es < Es && a < R) ? Gs[(int64_t(a) * Vs + vs) * Es + es] : 0.f;
-            }
+            for (int c = 0; c < 2; ++c) y[c][k] = Gs[(int64_t(min(16 * c + r, R - 1)) * Vs + vs) * Es + ec];
         }
+    };
+    auto madd = [&](const float (&x)[NT][NKS], const float (&y)[2][NKS]) {
 #pragma unroll
-        for (int k = 0; k < NKS; ++k)
+        for (int k = 0; k < NKS; ++k) {
+            const uint32_t me = mask_if(NKS * q + k < Es);
+            float yc[2];
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+            for (int c = 0; c < 2; ++c) yc[c] = masked(y[c][k], me & mask_if(16 * c + r < R));
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const float xt = masked(x[t][k], me);
 #pragma unroll
                 for (int c = 0; c < 2; ++c)
-                    acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[t][k], gb[c][k], acc[t][c], 0, 0, 0);
+                    acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(xt, yc[c], acc[t][c], 0, 0, 0);
+            }
+        }
+    };
+    if (u0 < u1) load(u0, sa[0], gb[0]);
+    for (int u = u0; u < u1; u += 2) {
+        if (u + 1 < u1) load(u + 1, sa[1], gb[1]);
+        madd(sa[0], gb[0]);
+        if (u + 1 >= u1) break;
+        if (u + 2 < u1) load(u + 2, sa[0], gb[0]);
+        madd(sa[1], gb[1]);
     }
     // waves 1..3 hand their sums to wave 0, which adds them in wave order
     for (int w = 1; w < 4; ++w) {
@@ -946,25 +989,28 @@ __global__ __launch_bounds__(256) void embed_dglast_mfma_kernel(const int *__res
         float aa[2][NKE], sb[NKE];
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            const int a = 16 * c + r;
-            if (a < R && ar && sE == 1 && (NKE & 3) == 0) {
-                const float4 *p4 = reinterpret_cast<const float4 *>(ar + int64_t(a) * sR + NKE * q);
+            const int a = 16 * c + r, ac = min(a, R - 1);
+            const uint32_t ma = mask_if(a < R);
+            if (ar && sE == 1 && (NKE & 3) == 0) {
+                const float4 *p4 = reinterpret_cast<const float4 *>(ar + int64_t(ac) * sR + NKE * q);
 #pragma unroll
                 for (int k4 = 0; k4 < NKE / 4; ++k4) {
                     const float4 v = p4[k4];
-                    aa[c][4 * k4] = v.x;
-                    aa[c][4 * k4 + 1] = v.y;
-                    aa[c][4 * k4 + 2] = v.z;
-                    aa[c][4 * k4 + 3] = v.w;
+                    aa[c][4 * k4] = masked(v.x, ma);
+                    aa[c][4 * k4 + 1] = masked(v.y, ma);
+                    aa[c][4 * k4 + 2] = masked(v.z, ma);
+                    aa[c][4 * k4 + 3] = masked(v.w, ma);
                 }
             } else {
 #pragma unroll
                 for (int k = 0; k < NKE; ++k)
-                    aa[c][k] = a < R ? (ar ? ar[int64_t(NKE * q + k) * sE + int64_t(a) * sR] : 1.f) : 0.f;
+                    aa[c][k] = masked(ar ? ar[int64_t(NKE * q + k) * sE + int64_t(ac) * sR] : 1.f, ma);
             }
         }
+        const int re = min(r, Es - 1);
+        const uint32_t mr = mask_if(r < Es);
 #pragma unroll
-        for (int k = 0; k < NKE; ++k) sb[k] = r < Es ? su[(NKE * q + k) * Es + r] : 0.f;
+        for (int k = 0; k < NKE; ++k) sb[k] = masked(su[(NKE * q + k) * Es + re], mr);
 #pragma unroll
         for (int k = 0; k < NKE; ++k)
 #pragma unroll
@@ -1090,14 +1136,14 @@ int launch_embed_sort(const int64_t *ids, int n, int64_t V, int passes, const Em
     int *bad = w.hist + 256 * nblk;
     const uint32_t *kin = nullptr, *vin = nullptr;
     uint32_t *kout = w.keysA, *vout = w.valsA;
+    // up to 64 blocks, each scatter workgroup scans the histograms itself
+    const int self_scan = nblk <= 64 ? 1 : 0;
     for (int p = 0; p < passes; ++p) {
         // pass 0 also clears the buffers, counts out-of-range ids and sets meta[0]
         const int nclr = p == 0 ? int(std::min<int64_t>(2048, std::max<int64_t>(1, (nclear + nzero + 4095) / 4096))) : 0;
         COMERA_LAUNCH(radix_hist_kernel, dim3(nblk + nclr), dim3(256), 0, hipStream_t(stream), ids, kin, n, V,
-                           8 * p, nblk, w.hist, p == 0 ? bad : nullptr, err_flag, w.headpos, p == 0 ? nclear : 0,
+                           8 * p, nblk, w.hist, self_scan, p == 0 ? bad : nullptr, err_flag, w.headpos, p == 0 ? nclear : 0,
                            zero, p == 0 ? nzero : 0);
-        // up to 64 blocks, each scatter workgroup scans the histograms itself
-        const int self_scan = nblk <= 64 ? 1 : 0;
         if (!self_scan)
             COMERA_LAUNCH(radix_scan_kernel, dim3(1), dim3(1024), 0, hipStream_t(stream), w.hist, nblk,
                                p == 0 ? bad : nullptr, n, w.meta);
@@ -1117,7 +1163,8 @@ int launch_embed_segsum(const float *dY, int E, int n, int passes, const EmbedWs
     COMERA_LAUNCH(embed_segsum_kernel, dim3(chunks), dim3(256), 0, hipStream_t(stream), dY, E, w.meta, keys, vals,
                        w.S, w.Pfirst, w.Plast, w.headpos);
     if (int e = launch_status()) return e;
-    COMERA_LAUNCH(embed_segfix_kernel, dim3(chunks, unsigned((E + 63) / 64)), dim3(256), 0, hipStream_t(stream),
+    const int vecs = E % 4 == 0 ? E / 4 : E;
+    COMERA_LAUNCH(embed_segfix_kernel, dim3(chunks, unsigned((vecs + 63) / 64)), dim3(256), 0, hipStream_t(stream),
                        E, w.meta, keys, w.Pfirst, w.Plast, w.S);
     return launch_status();
 }
