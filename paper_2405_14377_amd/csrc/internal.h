@@ -153,6 +153,7 @@ struct ChainArgs {
     const float *D[kMaxCores];
     uint8_t amap[kMaxCores + 1][kChainMaxRank];
     int d, TB, act_bf16;
+    int split;                          // backward: one workgroup per token group and output
     int r[kMaxCores + 1], rc[kMaxCores + 1], m[kMaxCores], n[kMaxCores];
     int Nl[kMaxCores], Mg[kMaxCores];   // prod of n before core k, prod of m after core k
     int ssz[kMaxCores + 1];             // floats of state k per token
