@@ -578,10 +578,12 @@ __global__ __launch_bounds__(256) void tt_build_kernel(ChainsArgs a) {
     if (fold) {
         const int nb = (a.blk[2] - a.blk[1]) / 2;
         for (int j = 2; j <= q; ++j) {
-            const int rp = h.rp[j], S = h.S[j - 1], total = h.r[j - 1] * S * rp;
-            for (int o = ((blk - a.blk[1]) >> 1) * 256 + t; o < total; o += nb * 256) {
+            // below 2^31 entries (layout_bottleneck): unsigned, so that the
+            // step past the end does not wrap
+            const uint32_t rp = h.rp[j], S = h.S[j - 1], total = uint32_t(h.r[j - 1]) * S * rp;
+            for (uint32_t o = ((blk - a.blk[1]) >> 1) * 256 + t; o < total; o += nb * 256) {
                 const int c = o % rp, u = o / rp, cp = u / S;
-                h.C[j][o] = c < h.r[j] ? core_at(l, j, cp, u - cp * S, c) * l.D[j - 1][rev ? cp : c] : 0.f;
+                h.C[j][o] = c < h.r[j] ? core_at(l, j, cp, u - cp * int(S), c) * l.D[j - 1][rev ? cp : c] : 0.f;
             }
         }
         return;
@@ -970,6 +972,9 @@ bool layout_bottleneck(const comera_ttm_plan_s *p, const SweepLayout &L, size_t 
             const int64_t S = g == 0 ? p->s.n[k] : p->s.m[k];
             const int64_t rprev = i == 0 ? 1 : (g == 0 ? p->rho[k] : p->rho[k + 1]);
             const int64_t r = g == 0 ? p->rho[k + 1] : p->rho[k], rp = i + 1 == q ? B.RP : (r + 15) / 16 * 16;
+            // the folded core, at its padded rank, is indexed with 32 bits (the
+            // plan bounds the unpadded core only)
+            if (i > 0 && double(rprev) * double(S) * double(rp) >= 2147483648.0) return false;
             if (i > 0) B.c[g][i + 1] = region(4.0 * double(rprev * S * rp));
             n *= S;
             if (n * 64 > (int64_t(1) << 30)) return false;
