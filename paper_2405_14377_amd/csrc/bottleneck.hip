@@ -109,6 +109,7 @@ struct PassArgs {
     const void *in, *op1, *op2;
     void *out, *state;
     int64_t K, N, b, spitch;
+    int R;                       // state entries R .. RP are padding
     int vec_in, vec_out;
 };
 constexpr int kPassWaves = 8;
@@ -192,6 +193,10 @@ __global__ __launch_bounds__(64 * kPassWaves) void tt_pass_kernel(PassArgs a) {
         f32x4 v = *reinterpret_cast<const f32x4 *>(red);
 #pragma unroll
         for (int w = 1; w < NW; ++w) v += *reinterpret_cast<const f32x4 *>(red + w * TOK * RPITCH);
+        // an infinity times the zeros of op1 would leave NaN in the padding,
+        // which the zeros of op2 carried into the whole row of out
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = 4 * r4 + e < a.R ? v[e] : 0.f;
         if constexpr (sizeof(T) == 2) {
             u32x2 h;
             h[0] = pack2(v[0], v[1]);
@@ -292,6 +297,7 @@ struct MeetArgs {
     int strips0;                 // column strips of problem 0
     int64_t b, spitch, kchunk, split_stride;
     float *part;
+    int R;                       // columns R .. RP of a partial are padding: zeros, also beside infinities in V
     int vec[2];
 };
 
@@ -437,7 +443,7 @@ __global__ __launch_bounds__(64 * kMeetWaves) void tt_meet_bf16_kernel(MeetArgs 
             const int64_t col = c0 + 16 * c + 4 * lg + v;
             if (col < C)
 #pragma unroll
-                for (int r = 0; r < RB; ++r) out[col * RP + 16 * r + lr] = acc[c][r][v];
+                for (int r = 0; r < RB; ++r) out[col * RP + 16 * r + lr] = 16 * r + lr < a.R ? acc[c][r][v] : 0.f;
         }
 }
 
@@ -488,7 +494,7 @@ __global__ __launch_bounds__(64 * kMeetWaves) void tt_meet_f32_kernel(MeetArgs a
             const int64_t col = c0 + 4 * (4 * lg + v) + j;
             if (col < C)
 #pragma unroll
-                for (int r = 0; r < RB; ++r) out[col * RP + RB * lr + r] = acc[j][r][v];
+                for (int r = 0; r < RB; ++r) out[col * RP + RB * lr + r] = RB * lr + r < a.R ? acc[j][r][v] : 0.f;
         }
 }
 
@@ -894,6 +900,7 @@ int pass(const comera_ttm_plan_s *p, int64_t b, const void *in, int64_t K, size_
     a.N = N;
     a.b = b;
     a.spitch = B.spitch;
+    a.R = B.R;
     a.vec_in = al16(in);
     a.vec_out = al16(out);
     return p->s.act == COMERA_BF16 ? go_pass<uint16_t>(a, B.RP, stream) : go_pass<float>(a, B.RP, stream);
@@ -926,6 +933,7 @@ int meet(const comera_ttm_plan_s *p, int64_t b, const void *X, const void *dY, v
     a.strips0 = int((p->N_in + sw - 1) / sw);
     a.b = b;
     a.spitch = B.spitch;
+    a.R = B.R;
     a.kchunk = B.kchunk;
     splits = int((b + B.kchunk - 1) / B.kchunk);
     a.split_stride = (p->N_in + p->N_out) * B.RP;

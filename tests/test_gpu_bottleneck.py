@@ -153,3 +153,29 @@ def test_partial_outputs():
     C.comera_ttm_backward(run.plan.handle, 90, Xt, dYt, run.G, run.D, None, some, run.ws)
     for k in (1, 4):
         assert rel_err(to_np(some[k]), dGr[k]) <= 1e-4
+
+
+@pytest.mark.parametrize("act", ["f32", "bf16"])
+@pytest.mark.parametrize("where", ["X", "dY"])
+@pytest.mark.parametrize("ranks", [(3, 1, 2), (6, 30, 7), (6, 33, 7)], ids=["R1", "R30", "R33"])
+def test_infinities_stay_infinities(ranks, where, act):
+    """One infinite activation among positive values and positive cores: every
+    result it reaches is that infinity (a rank padded with zeros must not turn
+    it into NaN), every other one is as finite as in the oracle."""
+    n, m, r = _layout((4, 6), (8, 4), ranks)
+    b = 40
+    rng = np.random.default_rng(241)
+    cores = [rng.uniform(0.5, 1.0, (r[k], m[k], n[k], r[k + 1])).astype(np.float32) for k in range(4)]
+    X, dY = (rng.integers(1, 5, (b, w)).astype(np.float32) for w in (24, 32))
+    (X if where == "X" else dY)[17, 9] = np.inf
+    Yr = OT.forward_dense(X, cores)
+    dXr, dGr = OT.backward_dense(X, dY, cores)
+    run = TTMRun(n, m, r, cores, None, b, act, force_order=_order(n, m, r, act, b, 2))
+    Xt, dYt = to_dev(X, act), to_dev(dY, act)
+    got = [run.forward(Xt)]
+    dX, dG = run.backward(Xt, dYt)
+    for g, ref in zip(got + [dX] + dG, [Yr, dXr] + dGr):
+        g, fin = to_np(g), np.isfinite(ref)
+        assert not np.isnan(ref).any() and np.array_equal(np.isposinf(g), ~fin)
+        if fin.any():
+            assert rel_err(g[fin], ref[fin]) <= TOL[act]
