@@ -952,6 +952,43 @@ int meet(const comera_ttm_plan_s *p, int64_t b, const void *X, const void *dY, v
 
 comera_status status_of(int e) { return e ? COMERA_ERR_HIP : COMERA_OK; }
 
+// Where these kernels beat the general sweep (times of a training step there
+// and here):
+// - Batch-free work: a workgroup of the build forms the last mode's S x RP
+//   entries with 256 threads, each a sum over the K entries of the bond
+//   before it, loaded 16 at a time; up to 16 such rounds one after another
+//   (modes of 16 at rank 64, of 64 at rank 32) stay below the general build's
+//   launches.  64 and 48 modes at rank 64, 48 rounds, bf16, 4096 tokens: 136
+//   against 189 us; 1024 modes at rank 32, 256 tokens: 110 against 507 us;
+//   16 rounds (64 and 64 modes at rank 32, 4096 tokens): 171 against 125 us.
+// - fp32 at a padded rank of 64 is bound by the matrix units, which the
+//   GEMM's larger tiles use better once there are tokens enough to fill the
+//   chip with them: 768 -> 3072 r48 at 16384 tokens 502 against 451 us, at
+//   32768 tokens 732 against 808 us.  Over a few tokens one workgroup's pass
+//   is as long as over 16: 3840 -> 64 r64, 4 tokens, 130 against 151 us; 1024
+//   -> 4096 r48, 100 tokens, level.
+// - A pass gives 16 to 64 whole rows to one workgroup.  Over few tokens a few
+//   CUs then walk wide rows that the GEMM splits (1536 -> 12288 r32 fp32, 10
+//   tokens: 151 against 177 us), and fp32 rows or states of two padded groups
+//   fall behind the GEMM's stores at any batch (384 -> 6144 r32 fp32, 19460
+//   tokens: level; 128 -> 15360 r1, 17169 tokens: 989 against 1223 us; 5120 ->
+//   10240 r64 bf16, 675 tokens: 174 against 255 us).  Rows of up to 4096 are
+//   faster here in every form (1024 -> 4096 r64 fp32, 8192 tokens: 366 against
+//   341 us); bf16 at a padded rank of 32 from 512 tokens on at every width
+//   (768 -> 8000 r24, 6252 tokens: 197 against 133 us; 32768 -> 32768 r32,
+//   4096 tokens: 827 against 658 us).
+bool faster_here(const comera_ttm_plan_s *p, const SweepLayout &L, int RP) {
+    for (int g = 0; g < 2; ++g) {
+        const int q = L.e[g] - L.s[g] + 1, k = core_of(L, g, q - 1);
+        const int64_t S = g == 0 ? p->s.n[k] : p->s.m[k];
+        const int64_t K = q == 1 ? 1 : (g == 0 ? p->rho[k] : p->rho[k + 1]);
+        if ((S * RP + 255) / 256 * ((K + 15) / 16) > 16) return false;
+    }
+    const int64_t esz = p->s.act == COMERA_BF16 ? 2 : 4;
+    if (esz == 4 && RP == 64 && (p->batch < 64 || p->batch > 16384)) return false;
+    return std::max(p->N_in, p->N_out) <= 4096 || (esz == 2 && RP == 32 && p->batch >= 512);
+}
+
 }  // namespace
 
 bool layout_bottleneck(const comera_ttm_plan_s *p, const SweepLayout &L, size_t cap, BottleneckLayout &B) {
@@ -966,6 +1003,7 @@ bool layout_bottleneck(const comera_ttm_plan_s *p, const SweepLayout &L, size_t 
     B.RP = B.R <= 32 ? 32 : 64;
     const int64_t b = std::max<int64_t>(p->batch, 1);
     B.spitch = (b + 63) / 64 * 64;
+    if (!faster_here(p, L, B.RP)) return false;
     double off = 0;
     auto region = [&](double bytes) {
         const size_t o = size_t(off);

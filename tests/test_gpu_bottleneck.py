@@ -163,7 +163,7 @@ def test_infinities_stay_infinities(ranks, where, act):
     result it reaches is that infinity (a rank padded with zeros must not turn
     it into NaN), every other one is as finite as in the oracle."""
     n, m, r = _layout((4, 6), (8, 4), ranks)
-    b = 40
+    b = 72
     rng = np.random.default_rng(241)
     cores = [rng.uniform(0.5, 1.0, (r[k], m[k], n[k], r[k + 1])).astype(np.float32) for k in range(4)]
     X, dY = (rng.integers(1, 5, (b, w)).astype(np.float32) for w in (24, 32))

@@ -61,3 +61,35 @@ def layer_kernels(n, m, r, act, b, order=-1, want_dx=True, want_dg=True, reuse=T
 def test_one_bond_refuses_cores_past_32_bits(act, n, m, r):
     fwd, bwd, _ = layer_kernels(n, m, r, act, 16, "sweep-lr [0,1][2]")
     assert "tt_build_kernel" not in fwd + bwd
+
+
+def _tt(ins, outs, rank):
+    k, q = len(ins), len(ins) + len(outs)
+    desc = "sweep-lr [" + ",".join(map(str, range(k))) + "][" + ",".join(map(str, range(k, q))) + "]"
+    return ins + (1,) * len(outs), (1,) * k + outs, (1,) + (rank,) * (q - 1) + (1,), desc
+
+
+@pytest.mark.parametrize("act,ins,outs,rank,b,own", [
+    # rounds of the build: 16 and 17 over modes of 64 and 65 x 8
+    ("bf16", (64, 64), (64, 64), 32, 4096, True), ("bf16", (64, 64), (72, 64), 32, 4096, False),
+    ("f32", (64, 72), (64, 64), 32, 4096, False), ("bf16", (32, 24), (48, 64), 64, 4096, False),
+    ("bf16", (8, 8, 12), (16, 16, 16), 64, 4096, True), ("bf16", (8, 8, 12), (17, 16, 16), 64, 4096, False),
+    ("f32", (128,), (128,), 32, 4096, True), ("f32", (768,), (768,), 32, 4096, False),
+    # fp32 at a padded rank of 64 over few and many tokens
+    ("f32", (8, 8, 12), (16, 16, 12), 33, 63, False), ("f32", (8, 8, 12), (16, 16, 12), 33, 64, True),
+    ("f32", (8, 8, 12), (16, 16, 12), 48, 16384, True), ("f32", (8, 8, 12), (16, 16, 12), 48, 16385, False),
+    ("f32", (8, 8, 12), (16, 16, 12), 32, 16385, True), ("bf16", (8, 8, 12), (16, 16, 12), 48, 16385, True),
+    # rows past 4096 columns
+    ("f32", (8, 8, 12), (16, 16, 16), 32, 7, True), ("f32", (8, 8, 12), (16, 16, 16), 48, 4096, True),
+    ("f32", (8, 8, 12), (17, 16, 16), 32, 4096, False), ("bf16", (8, 8, 12), (16, 16, 16), 40, 7, True),
+    ("bf16", (8, 8, 12), (17, 16, 16), 32, 511, False), ("bf16", (8, 8, 12), (17, 16, 16), 32, 512, True),
+    ("bf16", (8, 8, 12), (17, 16, 14), 40, 512, True), ("bf16", (8, 8, 12), (16, 24, 16), 40, 512, False),
+])
+def test_one_bond_kernels_where_they_are_faster(act, ins, outs, rank, b, own):
+    n, m, r, desc = _tt(ins, outs, rank)
+    fwd, bwd, _ = layer_kernels(n, m, r, act, b, desc)
+    if own:
+        assert fwd == ["tt_build_kernel", "tt_pass_kernel"]
+        assert bwd[:2] == ["tt_pass_kernel", "tt_meet_kernel"] and bwd[-1] == "tt_grad_kernel"
+    else:
+        assert not [k for k in fwd + bwd if k.startswith("tt_")]
