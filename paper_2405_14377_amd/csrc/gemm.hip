@@ -1845,12 +1845,43 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void gemm_skinny_kernel(GemmPara
     }
 }
 
+// Where the kernel above is faster than split-K tiles.  Each workgroup reads
+// all rows of A and walks K with eight waves, so it loses where K x rows is
+// long, where many columns read A again and again, and where few columns
+// leave CUs idle that a split of K would fill (forward calls of a layer with
+// its W build, split K against this kernel):
+//   bf16, up to 16 rows: K <= 4096 (4096 -> 512: 19.6 against 18.6 us; 8192 ->
+//     512: 1.06 times as long here), N <= 8192 (512 -> 16384: 1.24)
+//   bf16, 32 rows: K <= 1024 (1024 -> 768: 0.82; 4096 -> 512: 1.14), or
+//     K <= 2048 with 2048 to 4096 columns (0.92)
+//   bf16, 64 rows: K <= 768 (768 -> 768: 0.84; 1024 -> 512: 1.03; 4096 -> 512:
+//     19.9 against 31.8 us), or K <= 1536 with 2048 to 4096 columns (0.84)
+//   fp32, up to 16 rows: everywhere (8192 -> 512: 0.78; 4096 -> 4096: 0.98)
+//   fp32, 32 rows: K <= 3072 (3072 -> 768: 0.81; 4096 -> 4096: 1.04) but for
+//     K between 1024 and 2048 with less than 2048 columns (1280 -> 512: 1.07)
+//   fp32, 64 rows: K <= 768 with 2048 to 8192 columns (768 -> 4096: 0.75;
+//     768 -> 512: 1.02; 4096 -> 512: 1.39)
+bool skinny_faster(const GemmArgs &g) {
+    const int64_t K = g.K, N = g.N;
+    const bool mid = N >= 2048 && N <= 4096;
+    if (g.dtype == COMERA_BF16) {
+        if (N > 8192) return false;
+        if (g.M <= 16) return K <= 4096;
+        if (g.M <= 32) return K <= 1024 || (mid && K <= 2048);
+        return K <= 768 || (mid && K <= 1536);
+    }
+    if (g.M <= 16) return true;
+    if (g.M <= 32) return K <= 3072 && (K <= 1024 || K >= 2048 || N >= 2048);
+    return K <= 768 && N >= 2048 && N <= 8192;
+}
+
 // Products of the kernel above: K-contiguous operands in whole 16-byte chunks,
-// a plain row-major result, at most 64 rows, and at least 32 workgroups of
-// columns (with fewer, splitting K over the grid fills more of the chip).
+// a plain row-major result, at most 64 rows, at least 32 workgroups of columns,
+// and no split of K asked for (an fp32 dX that the plan has split keeps its
+// splits).  N and K up to 16384: what was measured.
 bool skinny_ok(const GemmArgs &g) {
     if (g.dtype == kDtypeFp8 || !g.a_kc || !g.b_kc || g.oscale || g.splits > 1 || g.fast != -1 || g.tile != -1) return false;
-    if (g.M > 64 || g.N < 512 || g.N >= (int64_t(1) << 31) || g.K < 1 || g.K > 16384) return false;
+    if (g.M > 64 || g.N < 512 || g.N > 16384 || g.K < 1 || g.K > 16384 || !skinny_faster(g)) return false;
     if (g.rmap.nd != 1 || g.cmap.nd != 1 || g.cmap.stride[0] != 1) return false;
     const int64_t e = g.dtype == COMERA_BF16 ? 8 : 4;
     if (g.K % e || g.lda % e || g.ldb % e) return false;

@@ -93,3 +93,35 @@ def test_one_bond_kernels_where_they_are_faster(act, ins, outs, rank, b, own):
         assert bwd[:2] == ["tt_pass_kernel", "tt_meet_kernel"] and bwd[-1] == "tt_grad_kernel"
     else:
         assert not [k for k in fwd + bwd if k.startswith("tt_")]
+
+
+# ------------------------------------------------------------------ products of few rows
+_F = {512: (8, 8, 8), 768: (8, 8, 12), 1000: (10, 10, 10), 1024: (8, 8, 16), 1280: (8, 10, 16), 1536: (8, 12, 16),
+      2048: (8, 16, 16), 3072: (16, 16, 12), 4096: (16, 16, 16), 8192: (16, 16, 32), 16384: (32, 16, 32),
+      496: (8, 2, 31), 770: (7, 10, 11), 792: (9, 11, 8), 680: (5, 8, 17)}
+
+
+@pytest.mark.parametrize("act,K,N,b,own", [
+    ("bf16", 768, 3072, 1, True), ("bf16", 4096, 512, 16, True), ("bf16", 8192, 512, 16, False),
+    ("bf16", 512, 8192, 16, True), ("bf16", 512, 16384, 16, False), ("bf16", 768, 496, 16, False),
+    ("bf16", 1024, 768, 32, True), ("bf16", 1280, 512, 17, False), ("bf16", 2048, 4096, 32, True),
+    ("bf16", 3072, 4096, 32, False), ("bf16", 2048, 8192, 32, False), ("bf16", 768, 3072, 33, True),
+    ("bf16", 768, 512, 64, True), ("bf16", 1024, 512, 64, False), ("bf16", 1536, 4096, 64, True),
+    ("bf16", 2048, 4096, 64, False), ("bf16", 4096, 512, 64, False), ("bf16", 768, 3072, 65, False),
+    ("bf16", 770, 768, 7, False), ("bf16", 680, 792, 33, True),
+    ("f32", 16384, 512, 16, True), ("f32", 4096, 4096, 16, True), ("f32", 1024, 512, 32, True),
+    ("f32", 1280, 512, 32, False), ("f32", 1280, 2048, 32, True), ("f32", 3072, 768, 32, True),
+    ("f32", 4096, 512, 32, False), ("f32", 768, 3072, 64, True), ("f32", 768, 512, 64, False),
+    ("f32", 1000, 3072, 64, False), ("f32", 768, 16384, 64, False), ("f32", 768, 3072, 65, False),
+])
+def test_few_rows_kernel_where_it_is_faster(act, K, N, b, own):
+    fwd, _, _ = layer_kernels(_F[K], _F[N], (1, 4, 4, 1), act, b, 0)
+    assert ("gemm_skinny_kernel" in fwd) == own
+
+
+def test_few_rows_dx_keeps_the_splits_of_the_plan():
+    """fp32 dX over N_out >= 1024 is split over K by the plan and stays so;
+    bf16 and narrower fp32 layers take the few-rows kernel."""
+    assert "gemm_skinny_kernel" not in layer_kernels(_F[768], _F[3072], (1, 4, 4, 1), "f32", 7, 0, want_dg=False)[1]
+    assert "gemm_skinny_kernel" in layer_kernels(_F[768], _F[3072], (1, 4, 4, 1), "bf16", 7, 0, want_dg=False)[1]
+    assert "gemm_skinny_kernel" in layer_kernels(_F[680], _F[792], (1, 4, 4, 1), "f32", 7, 0, want_dg=False)[1]
