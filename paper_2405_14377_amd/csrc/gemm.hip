@@ -1539,7 +1539,7 @@ int launch_dma32(const GemmArgs &g, const GemmParams &p, void *stream) {
     const dim3 grid = tile_grid(g, 128, 128, q);
     if (!grid.x) return int(hipErrorInvalidConfiguration);
     q.gw = choose_gw(g, 128, 128, g.splits);
-    COMERA_LAUNCH_NAMED("gemm_dma32_kernel", kern, grid, dim3(256), lds, hipStream_t(stream), q);
+    COMERA_LAUNCH_NAMED(TAIL ? "gemm_dma32_kernel<tail>" : "gemm_dma32_kernel", kern, grid, dim3(256), lds, hipStream_t(stream), q);
     return launch_status();
 }
 
@@ -1559,7 +1559,7 @@ int launch_dma(const GemmArgs &g, const GemmParams &p, void *stream) {
     const dim3 grid = tile_grid(g, 256, BN, q);
     if (!grid.x) return int(hipErrorInvalidConfiguration);
     q.gw = choose_gw(g, 256, BN, g.splits);
-    COMERA_LAUNCH_NAMED("gemm_dma_kernel", kern, grid, dim3(512), lds, hipStream_t(stream), q);
+    COMERA_LAUNCH_NAMED(TAIL ? "gemm_dma_mn_kernel<tail>" : "gemm_dma_kernel", kern, grid, dim3(512), lds, hipStream_t(stream), q);
     return launch_status();
 }
 
@@ -1909,6 +1909,28 @@ bool fast_ok_k(const GemmArgs &g, int64_t kchunk, int ktb) {
     return g.K % kt == 0 && kchunk % kt == 0;
 }
 
+// Products of M/N-contiguous operands whose K ends within a stage: where the
+// straight-to-LDS kernels beat the bounds-checked ones, k being the length of
+// a split.  Few tokens leave the large tiles waiting for their first loads and
+// their store (dW, bounds-checked against straight-to-LDS):
+//   fp32: from 200 tokens (3072 x 3072 x 200: 73 against 71 us, x 161: 61
+//     against 67, x 65: 34 against 50)
+//   bf16: from 300 tokens a split (1536 x 1536 x 385: 22 against 21 us, x 257:
+//     17 against 19, x 65: 14 against 16), at any length where the tiles fill
+//     every CU (4096 x 4096 x 16: 20 against 18)
+//   bf16 whose pieces of a row of C are no whole 16 bytes leave C unstaged,
+//     which takes a 256 x 256 tile as long as 1000 tokens of products: from
+//     800 tokens a split up to 64 tiles (1680 x 1680 x 4001, 832 a split: 75
+//     against 62 us; 1536 x 1000 x 2001, 512 a split: 30 against 36), from 1280
+//     beyond (3072 x 1800 x 3333, 1696 a split: 92 against 83 us; x 2001, 1024
+//     a split: 60 against 68)
+bool tail_faster(const GemmArgs &g, int64_t k, bool staged) {
+    if (g.dtype == COMERA_F32) return k >= 200;
+    const int64_t t256 = ceil_div(g.M, 256) * ceil_div(g.N, 256);
+    if (staged) return k >= 300 || t256 >= 256;
+    return k >= (t256 <= 64 ? 800 : 1280);
+}
+
 bool fast_ok(const GemmArgs &g, int64_t kchunk, int ktb, bool tail_ok = false) {
     const int64_t sz = g.dtype == COMERA_BF16 ? 2 : (g.dtype == kDtypeFp8 ? 1 : 4);
     const int64_t kt = ktb / sz;
@@ -2033,8 +2055,9 @@ int launch_gemm(const GemmArgs &g, void *stream) {
         const int64_t kt = ktb / esz;
         pf.kchunk = ceil_div(p.kchunk, kt) * kt;
         // the straight-to-LDS kernels of M/N-contiguous operands (dW) take a
-        // K that ends within a stage
-        const bool tail_ok = !g.a_kc && !g.b_kc && (fast == F256x256_dma || fast == F128x128_dma32);
+        // K that ends within a stage where they beat the bounds-checked ones
+        const bool tail_ok = !g.a_kc && !g.b_kc && (fast == F256x256_dma || fast == F128x128_dma32) &&
+                             tail_faster(gg, std::min(g.K, p.kchunk), p.stage_c);
         if (!fast_ok(gg, pf.kchunk, ktb, tail_ok)) {
             // a K that is a multiple of the 64-byte K row but not of the
             // 128-byte one keeps a fast 128 x 128 tile on 64-byte rows

@@ -1,7 +1,9 @@
 """GPU parity of dW = X^T dY on the straight-to-LDS kernels when the token
 count does not fill the last K stage (64 tokens in bf16, 32 in fp32): one
-token, one token less than a stage, an odd number in between, and a token
-count whose last split holds only the short stage.  Dense order; every dG_k
+token, one token less than a stage, an odd number in between, token counts
+whose last split holds only the short stage, a product of less than a stage
+in all, and splits on the other side of the rule, which the bounds-checked
+kernel takes (tests/test_routes.py checks which).  Dense order; every dG_k
 against the oracle (a row counted twice or left out shows as an error far
 above the tolerance: each token weighs about 1 / sqrt(b) of dW).
 
@@ -17,16 +19,24 @@ from tests.test_gpu_ttm import _inputs
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # (act, n, m, b): 512 x 512 bf16 takes 4 tiles x 8 splits of 320 tokens
+    # (act, n, m, b).  Splits of 288 tokens, too short for the straight-to-LDS
+    # tile: the bounds-checked kernel, last splits of 1, 63 and 225 tokens
     ("bf16", (8, 8, 8), (8, 8, 8), 2049 + 256),
     ("bf16", (8, 8, 8), (8, 8, 8), 2111 + 256),
-    ("bf16", (8, 8, 12), (12, 8, 8), 4001),
-    # 8 splits of 288 tokens: 7 full ones and 33 tokens
     ("bf16", (8, 8, 8), (8, 8, 8), 7 * 320 + 1),
-    # 768 x 768 fp32 takes 36 tiles x 8 splits
+    # 12 splits of 320 tokens and one of 161
+    ("bf16", (8, 8, 12), (12, 8, 8), 4001),
+    # 768 x 768 fp32: 7 splits of 288 tokens and one of 33, of 63
     ("f32", (8, 8, 12), (12, 8, 8), 2049),
     ("f32", (8, 8, 12), (12, 8, 8), 2079),
+    # 9 splits of 288 tokens and one of 13, less than a stage
     ("f32", (17, 8, 8), (8, 16, 8), 2605),
+    # a last split of one token, and of 127 (63 past a whole stage)
+    ("bf16", (8, 8, 12), (12, 8, 8), 12 * 320 + 1),
+    ("bf16", (8, 8, 8), (8, 8, 8), 20 * 320 + 127),
+    ("f32", (8, 8, 12), (12, 8, 8), 8 * 288 + 1),
+    # one split of less than a stage
+    ("bf16", (16, 16, 16), (16, 16, 16), 17),
 ]
 
 

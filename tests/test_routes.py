@@ -125,3 +125,30 @@ def test_few_rows_dx_keeps_the_splits_of_the_plan():
     assert "gemm_skinny_kernel" not in layer_kernels(_F[768], _F[3072], (1, 4, 4, 1), "f32", 7, 0, want_dg=False)[1]
     assert "gemm_skinny_kernel" in layer_kernels(_F[768], _F[3072], (1, 4, 4, 1), "bf16", 7, 0, want_dg=False)[1]
     assert "gemm_skinny_kernel" in layer_kernels(_F[680], _F[792], (1, 4, 4, 1), "f32", 7, 0, want_dg=False)[1]
+
+
+# ------------------------------------------------------------------ dW over a token count that ends within a stage
+@pytest.mark.parametrize("act,n,m,b,own", [
+    ("f32", (16, 16, 12), (16, 16, 12), 199, False), ("f32", (16, 16, 12), (16, 16, 12), 201, True),
+    ("f32", (16, 16, 16), (16, 16, 16), 17, False), ("f32", (8, 8, 12), (12, 8, 8), 2049, True),
+    ("bf16", (8, 12, 16), (16, 16, 12), 299, False), ("bf16", (8, 12, 16), (16, 16, 12), 301, True),
+    ("bf16", (16, 16, 16), (16, 16, 16), 17, True), ("bf16", (8, 8, 12), (12, 8, 8), 16001, True),
+    # a last output mode that is no whole number of 16-byte pieces
+    ("bf16", (12, 14, 10), (12, 14, 10), 3333, False), ("bf16", (12, 14, 10), (12, 14, 10), 4001, True),
+    ("bf16", (16, 16, 12), (12, 10, 15), 2001, False), ("bf16", (16, 16, 12), (12, 10, 15), 3333, True),
+])
+def test_dw_tail_where_it_is_faster(act, n, m, b, own):
+    _, bwd, _ = layer_kernels(n, m, (1, 4, 4, 1), act, b, 0, want_dx=False)
+    assert any(k.endswith("<tail>") for k in bwd) == own, bwd
+
+
+def test_dw_tail_of_the_gpu_cases():
+    """The GPU parity cases reach the kernel that they are for."""
+    from tests.test_gpu_dw_tail import CASES
+    own = []
+    for act, n, m, b in CASES:
+        _, bwd, _ = layer_kernels(n, m, (1, 6, 7, 1), act, b, 0, want_dx=False)
+        if any(k.endswith("<tail>") for k in bwd):
+            own.append((act, b))
+    assert own == [("bf16", 4001), ("f32", 2049), ("f32", 2079), ("f32", 2605), ("bf16", 3841), ("bf16", 6527),
+                   ("f32", 2305), ("bf16", 17)]
