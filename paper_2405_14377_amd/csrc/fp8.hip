@@ -70,37 +70,40 @@ __device__ __forceinline__ float chunk_absmax(const u32x4 v) {
     return m;
 }
 
-// The same maxima with 16-byte loads, eight in flight per thread; x 16-byte
+// The same maxima with 16-byte loads, U in flight per thread; x 16-byte
 // aligned.  Bound by HBM (40000 x 4096 bf16: 101 us as one contiguous range per
-// workgroup, 93 us in memory order).  Elements past the last whole chunk are taken by workgroup 0.
+// workgroup, 93 us in memory order).  Elements past the last whole chunk are
+// taken by workgroup 0.  U = 4 up to 64 MiB, so that the blocks of U chunks
+// reach all workgroups (16384 x 1024 bf16, 32 MiB, with the quantiser: 19.8
+// against 20.4 us with eight); U = 8 above (40000 x 4096 bf16: 182 against 180 us).
 constexpr int kAmaxThreads = 1024;   // 512 workgroups of 16 waves fill every SIMD
-template <int V>
+template <int V, int U>
 __global__ __launch_bounds__(kAmaxThreads) void amax_vec_kernel(const void *__restrict__ x, int dtype, int64_t n,
                                                                 float *__restrict__ pmax) {
     __shared__ float red[kAmaxThreads / 64];
     const u32x4 *xv = reinterpret_cast<const u32x4 *>(x);
     const int64_t nv = n / V;
-    // blocks of eight 16-byte chunks per thread, dealt out in memory order:
+    // blocks of U 16-byte chunks per thread, dealt out in memory order:
     // at any time the grid reads one moving window, so what it read last (as
     // much as the last-level cache holds) is what the quantiser reads first.
     // The next block loads while the current one is reduced.
-    constexpr int64_t kBlock = 8 * kAmaxThreads;
+    constexpr int64_t kBlock = U * kAmaxThreads;
     const int64_t step = gridDim.x * kBlock;
     int64_t i = blockIdx.x * kBlock + threadIdx.x;
     float m = 0.f;
-    u32x4 a[8];
+    u32x4 a[U];
     auto load = [&](int64_t j) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) a[u] = xv[min(j + u * kAmaxThreads, nv - 1)];   // repeats do not change a maximum
+        for (int u = 0; u < U; ++u) a[u] = xv[min(j + u * kAmaxThreads, nv - 1)];   // repeats do not change a maximum
     };
     if (i - threadIdx.x < nv) load(i);
     for (; i - threadIdx.x < nv; i += step) {
-        u32x4 c[8];
+        u32x4 c[U];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) c[u] = a[u];
+        for (int u = 0; u < U; ++u) c[u] = a[u];
         if (i - threadIdx.x + step < nv) load(i + step);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) m = fmaxf(m, chunk_absmax<V>(c[u]));
+        for (int u = 0; u < U; ++u) m = fmaxf(m, chunk_absmax<V>(c[u]));
     }
     if (blockIdx.x == 0)
         for (int64_t j = nv * V + threadIdx.x; j < n; j += kAmaxThreads) m = fmaxf(m, fabsf(load_act(x, dtype, j)));
@@ -222,17 +225,24 @@ __global__ __launch_bounds__(256) void quant_kernel(const void *__restrict__ x, 
 // Requires x 16-byte aligned, C % V == 0, q (if any) V-byte aligned with
 // ldq % V == 0, qt (if any) 16-byte aligned with ldt % 16 == 0: every chunk
 // then lies wholly inside or wholly outside each bound.  The grid covers
-// ceil(R' / 128) x ceil(C' / 128) tiles, ct per row of tiles, from the last row
-// of tiles to the first: the maximum pass before it has just read the end of x,
+// ceil(R' / 128) x ceil(C' / 128) tiles, all of a row of tiles together, from the
+// last row of tiles to the first: the maximum pass before it has just read the end of x,
 // as much of it as the last-level cache holds (40000 x 4096 bf16: 116 us from
-// the first row on and column tile by column tile, 100 us).
+// the first row on and column tile by column tile, 100 us).  by_col: from the
+// first row on, column tile by column tile.  Rows of tiles leave each XCD (a
+// workgroup in eight) the same columns, which fp32 rows of a few tiles spread
+// over too few channels: an fp32 x that the last-level cache holds whole, of
+// less than 4096 columns (16384 x 1024: 30.8 against 28.1 us both passes;
+// 8192 x 4096 the other way, 50.7 against 60.7; 131072 x 1024, 512 MiB, 237
+// against 256); a small bf16 x likewise (16384 x 768: 17.0 against 16.5;
+// 24000 x 1024 the other way, 24.4 against 25.1).
 constexpr int kQT = 128;
 template <int V>
 __global__ __launch_bounds__(256) void quant_vec_kernel(const void *__restrict__ x, int64_t R, int64_t C,
                                                         const float *__restrict__ pmax, int nb, uint8_t *__restrict__ q,
                                                         int64_t ldq, uint8_t *__restrict__ qt, int64_t ldt,
                                                         float *__restrict__ s_out, const float *pa, float *oa,
-                                                        const float *pb, float *ob, uint32_t ct) {
+                                                        const float *pb, float *ob, int by_col) {
     constexpr int CPR = kQT / V;             // chunks per tile row
     constexpr int RG = 256 / CPR;            // four-row groups per pass
     constexpr int NG = kQT / (4 * RG);       // passes
@@ -241,8 +251,8 @@ __global__ __launch_bounds__(256) void quant_vec_kernel(const void *__restrict__
     __shared__ __attribute__((aligned(16))) uint8_t tt[kQT][kQT];   // tt[c][r], 16-byte pieces swizzled
     const int tid = threadIdx.x;
     const int ch = tid % CPR, rg = tid / CPR;
-    const uint32_t t = gridDim.x - 1 - blockIdx.x;   // last rows first, all column tiles of a row tile together
-    const int64_t r0 = int64_t(t / ct) * kQT, c0 = int64_t(t % ct) * kQT;
+    const int64_t r0 = int64_t(by_col ? blockIdx.x : gridDim.y - 1 - blockIdx.y) * kQT;
+    const int64_t c0 = int64_t(by_col ? blockIdx.y : gridDim.x - 1 - blockIdx.x) * kQT;
     const int64_t c = c0 + int64_t(ch) * V;
     const char *xb = reinterpret_cast<const char *>(x);
     // every load of the tile first (addresses in bounds; zero selected after)
@@ -262,7 +272,7 @@ __global__ __launch_bounds__(256) void quant_vec_kernel(const void *__restrict__
     if ((tid & 63) == 0) red[tid >> 6] = m;
     __syncthreads();
     const float s = pow2_scale(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
-    if (blockIdx.x == 0 && tid == 0) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) {
         if (s_out) s_out[0] = s;
         if (pa && oa) *oa = 1.f / (s * *pa);
         if (pb && ob) *ob = 1.f / (s * *pb);
@@ -328,15 +338,18 @@ int launch_fp8_quant(const void *x, int dtype, int64_t R, int64_t C, float *pmax
     const bool xa = al(x, 16);
     int nb;
     if (xa) {
-        // at least four 16-byte loads per thread
-        const int64_t per = int64_t(kAmaxThreads) * 4;
-        nb = int(std::min<int64_t>(kAmaxBlocks, std::max<int64_t>(1, (n / V + per - 1) / per)));
+        const int64_t nv = n / V;
+        const bool wide = nv > int64_t(kAmaxBlocks) * 8 * kAmaxThreads;   // above 64 MiB
+        const int64_t per = int64_t(kAmaxThreads) * (wide ? 8 : 4);       // a workgroup's block
+        nb = int(std::min<int64_t>(kAmaxBlocks, std::max<int64_t>(1, (nv + per - 1) / per)));
+        auto go = [&](auto kern) {
+            COMERA_LAUNCH_NAMED(wide ? "amax_vec_kernel<wide>" : "amax_vec_kernel", kern, dim3(nb), dim3(kAmaxThreads),
+                                0, hipStream_t(stream), x, dtype, n, pmax);
+        };
         if (V == 8)
-            COMERA_LAUNCH(amax_vec_kernel<8>, dim3(nb), dim3(kAmaxThreads), 0, hipStream_t(stream), x, dtype, n,
-                               pmax);
+            wide ? go(amax_vec_kernel<8, 8>) : go(amax_vec_kernel<8, 4>);
         else
-            COMERA_LAUNCH(amax_vec_kernel<4>, dim3(nb), dim3(kAmaxThreads), 0, hipStream_t(stream), x, dtype, n,
-                               pmax);
+            wide ? go(amax_vec_kernel<4, 8>) : go(amax_vec_kernel<4, 4>);
     } else {
         nb = int(std::min<int64_t>(kAmaxBlocks, (n + 255) / 256));
         COMERA_LAUNCH(amax_partial_kernel, dim3(nb), dim3(256), 0, hipStream_t(stream), x, dtype, n, pmax);
@@ -344,18 +357,20 @@ int launch_fp8_quant(const void *x, int dtype, int64_t R, int64_t C, float *pmax
     if (int e = launch_status()) return e;
     const int64_t rows = qt ? std::max<int64_t>(R, ldt) : R;
     const int64_t cols = q ? std::max<int64_t>(C, ldq) : C;
-    const int64_t vx = (rows + kQT - 1) / kQT, vy = (cols + kQT - 1) / kQT;
-    const bool vec = xa && C % V == 0 && (!q || (al(q, V) && ldq % V == 0)) && (!qt || (al(qt, 16) && ldt % 16 == 0)) &&
-                     vy <= 65535 && vx <= 2147483647 / vy;   // one-dimensional grid
-    const int64_t gx = (rows + 63) / 64, gy = (cols + 63) / 64;
-    if (!vec && (gx > 2147483647 || gy > 65535)) return int(hipErrorInvalidValue);
-    const dim3 grid = vec ? dim3(static_cast<unsigned>(vx * vy)) : dim3(static_cast<unsigned>(gx), static_cast<unsigned>(gy));
+    const bool vec = xa && C % V == 0 && (!q || (al(q, V) && ldq % V == 0)) && (!qt || (al(qt, 16) && ldt % 16 == 0));
+    const int tile = vec ? kQT : 64;
+    const int64_t gx = (rows + tile - 1) / tile, gy = (cols + tile - 1) / tile;
+    if (gx > 2147483647 || gy > 65535) return int(hipErrorInvalidValue);
+    // tiles by row need the row tiles in the grid's y
+    const int by_col = gx > 65535 || (V == 4 ? C < 4096 && n * 4 <= (int64_t(256) << 20)
+                                             : C < 2048 && n * 2 <= (int64_t(40) << 20));
+    const dim3 grid = vec && !by_col ? dim3(unsigned(gy), unsigned(gx)) : dim3(unsigned(gx), unsigned(gy));
     if (vec && V == 8)
         COMERA_LAUNCH(quant_vec_kernel<8>, grid, dim3(256), 0, hipStream_t(stream), x, R, C, pmax, nb, q, ldq,
-                           qt, ldt, s_out, pa, oa, pb, ob, uint32_t(vy));
+                           qt, ldt, s_out, pa, oa, pb, ob, by_col);
     else if (vec)
         COMERA_LAUNCH(quant_vec_kernel<4>, grid, dim3(256), 0, hipStream_t(stream), x, R, C, pmax, nb, q, ldq,
-                           qt, ldt, s_out, pa, oa, pb, ob, uint32_t(vy));
+                           qt, ldt, s_out, pa, oa, pb, ob, by_col);
     else
         COMERA_LAUNCH(quant_kernel, grid, dim3(256), 0, hipStream_t(stream), x, dtype, R, C, pmax, nb, q, ldq,
                            qt, ldt, s_out, pa, oa, pb, ob);

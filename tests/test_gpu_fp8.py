@@ -101,6 +101,31 @@ def test_quantize_bit_exact(case):
     assert np.array_equal(q2, q_ref) and np.array_equal(qt2, qt_ref)
 
 
+@pytest.mark.parametrize("act,rows,cols,where", [
+    ("f32", 300, 1000, 0), ("f32", 300, 4100, 0),                # tiles by column, by row
+    ("bf16", 8192, 4096, -1), ("bf16", 8192, 4104, -1),          # 64 MiB, just above: four and eight loads a thread
+    ("f32", 4099, 4096, -1), ("bf16", 130, 1032, 130 * 1032 // 2),
+], ids=lambda x: str(x))
+def test_quantize_tile_orders_and_large_tensors(act, rows, cols, where):
+    """The maximum alone sets the scale wherever it sits, and every code is
+    the value times that scale, rounded: the same codes as torch's E4M3
+    conversion of the exact product x s (a power of two, no saturation)."""
+    import torch
+    x = torch.randn((rows, cols), generator=torch.Generator().manual_seed(5)).to(torch.bfloat16 if act == "bf16" else torch.float32)
+    x.view(-1)[where] = 100.0
+    x = x.to("cuda")
+    ldq, ldt = (cols + 127) // 128 * 128, (rows + 127) // 128 * 128
+    q = torch.full((rows, ldq), 0xAA, dtype=torch.uint8, device="cuda")
+    qt = torch.full((cols, ldt), 0xAA, dtype=torch.uint8, device="cuda")
+    s = torch.zeros(1, dtype=torch.float32, device="cuda")
+    ws = torch.empty(C.FP8_QUANTIZE_WS_BYTES, dtype=torch.uint8, device="cuda")
+    C.comera_fp8_quantize(x, C.BF16 if act == "bf16" else C.F32, rows, cols, q, ldq, qt, ldt, s, ws)
+    assert float(s.item()) == 4.0                                # 100 * 4 <= 448 < 100 * 8
+    ref = (x.float() * 4.0).to(torch.float8_e4m3fn).view(torch.uint8)
+    assert torch.equal(q[:, :cols], ref) and not q[:, cols:].any()
+    assert torch.equal(qt[:, :rows], ref.t()) and not qt[:, rows:].any()
+
+
 EXACT_CASES = [((8, 8, 12), (12, 8, 8), (1, 8, 8, 1), 200),
                ((4, 8, 4, 8), (8, 8, 8, 8), (1, 16, 16, 16, 1), 130),
                ((16, 8, 8, 1, 1, 1), (1, 1, 1, 8, 8, 16), (1, 4, 4, 4, 4, 4, 1), 64),

@@ -152,3 +152,23 @@ def test_dw_tail_of_the_gpu_cases():
             own.append((act, b))
     assert own == [("bf16", 4001), ("f32", 2049), ("f32", 2079), ("f32", 2605), ("bf16", 3841), ("bf16", 6527),
                    ("f32", 2305), ("bf16", 17)]
+
+
+# ------------------------------------------------------------------ FP8 quantiser
+@pytest.mark.parametrize("act,rows,cols,name,nb", [
+    ("bf16", 64, 64, "amax_vec_kernel", 1), ("bf16", 16384, 1024, "amax_vec_kernel", 512),
+    ("bf16", 8192, 1024, "amax_vec_kernel", 256), ("bf16", 8192, 4096, "amax_vec_kernel", 512),
+    ("bf16", 8192, 4104, "amax_vec_kernel<wide>", 512), ("f32", 16384, 1024, "amax_vec_kernel", 512),
+    ("f32", 40000, 4096, "amax_vec_kernel<wide>", 512),
+])
+def test_maximum_pass_leaves_no_workgroup_without_loads(act, rows, cols, name, nb):
+    C.comera_debug_launch_check(True)
+    try:
+        assert C.load().comera_fp8_quantize(fake(4 * rows * cols), ACT[act], rows, cols, fake(rows * cols), cols, None,
+                                            0, fake(4), fake(4096), C.FP8_QUANTIZE_WS_BYTES, 0) == C.OK
+        log = C.comera_debug_launch_log()
+    finally:
+        C.comera_debug_launch_check(False)
+    assert (log[0]["kernel"], log[0]["grid"][0]) == (name, nb)
+    chunks = rows * cols // (8 if act == "bf16" else 4)
+    assert (nb - 1) * 1024 * (8 if "wide" in name else 4) < chunks
