@@ -1016,28 +1016,25 @@ __global__ __launch_bounds__(256) void embed_dglast_mfma_kernel(const int *__res
         float aa[2][NKE], sb[NKE];
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            const int a = 16 * c + r, ac = min(a, R - 1);
-            const uint32_t ma = mask_if(a < R);
-            if (ar && sE == 1 && (NKE & 3) == 0) {
-                const float4 *p4 = reinterpret_cast<const float4 *>(ar + int64_t(ac) * sR + NKE * q);
+            const int a = 16 * c + r;
+            if (a < R && ar && sE == 1 && (NKE & 3) == 0) {
+                const float4 *p4 = reinterpret_cast<const float4 *>(ar + int64_t(a) * sR + NKE * q);
 #pragma unroll
                 for (int k4 = 0; k4 < NKE / 4; ++k4) {
                     const float4 v = p4[k4];
-                    aa[c][4 * k4] = masked(v.x, ma);
-                    aa[c][4 * k4 + 1] = masked(v.y, ma);
-                    aa[c][4 * k4 + 2] = masked(v.z, ma);
-                    aa[c][4 * k4 + 3] = masked(v.w, ma);
+                    aa[c][4 * k4] = v.x;
+                    aa[c][4 * k4 + 1] = v.y;
+                    aa[c][4 * k4 + 2] = v.z;
+                    aa[c][4 * k4 + 3] = v.w;
                 }
             } else {
 #pragma unroll
                 for (int k = 0; k < NKE; ++k)
-                    aa[c][k] = masked(ar ? ar[int64_t(NKE * q + k) * sE + int64_t(ac) * sR] : 1.f, ma);
+                    aa[c][k] = a < R ? (ar ? ar[int64_t(NKE * q + k) * sE + int64_t(a) * sR] : 1.f) : 0.f;
             }
         }
-        const int re = min(r, Es - 1);
-        const uint32_t mr = mask_if(r < Es);
 #pragma unroll
-        for (int k = 0; k < NKE; ++k) sb[k] = masked(su[(NKE * q + k) * Es + re], mr);
+        for (int k = 0; k < NKE; ++k) sb[k] = r < Es ? su[(NKE * q + k) * Es + r] : 0.f;
 #pragma unroll
         for (int k = 0; k < NKE; ++k)
 #pragma unroll
