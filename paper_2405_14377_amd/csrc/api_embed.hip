@@ -282,7 +282,7 @@ comera_status comera_tt_embed_backward_ex(const comera_tt_embed_shape *s, const 
     e = launch_embed_segsum(dY, int(dm.E), n, L.passes, w, stream);
     if (e) return COMERA_ERR_HIP;
     if (d == 1) return hip_status(launch_embed_gather(w, dm.V, int(dm.E), dG[0], stream));
-    e = launch_embed_dapre(w, G[d - 1], dm.Vp, int(dm.Ep), dm.R, dm.Vs, dm.Es, int(s->v[d - 2]), int(s->e[d - 2]),
+    e = launch_embed_dapre(w, n, G[d - 1], dm.Vp, int(dm.Ep), dm.R, dm.Vs, dm.Es, int(s->v[d - 2]), int(s->e[d - 2]),
                            stream);
     if (e) return COMERA_ERR_HIP;
     e = launch_embed_dglast(w, Apre, d >= 3, dm.Vp, int(dm.Ep), dm.R, dm.Vs, dm.Es, stream);

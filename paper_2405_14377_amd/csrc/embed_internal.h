@@ -54,7 +54,7 @@ const uint32_t *embed_sorted_keys(const EmbedWs &w, int passes);
 int launch_embed_segsum(const float *dY, int E, int n, int passes, const EmbedWs &w, void *stream);
 // dA [Vp][Ep][R] per prefix (written blocked for the prefix projections:
 // [(V', E')][(vq, eq)][R] with vp = V' vq + x, ep = E' eq + y)
-int launch_embed_dapre(const EmbedWs &w, const float *Gs, int64_t Vp, int Ep, int R, int Vs, int Es, int vq, int eq,
+int launch_embed_dapre(const EmbedWs &w, int64_t n, const float *Gs, int64_t Vp, int Ep, int R, int Vs, int Es, int vq, int eq,
                        void *stream);
 // dG_last partials, one per chunk of prefixes: [chunk][R][Vs][Es]
 int launch_embed_dglast(const EmbedWs &w, const float *Apre, bool rank_major, int64_t Vp, int Ep, int R, int Vs,

@@ -875,7 +875,18 @@ __global__ __launch_bounds__(256) void embed_dglast_kernel(const int *__restrict
 // The contraction index es runs in the order es = NKS q + k (k-th product,
 // lane group q), so each lane reads NKS consecutive floats of S_u and of
 // G_last.
-template <int NT, int NKS>
+//
+// AHEAD: the next id's operands load while the current ones are multiplied.
+// It hides latency where a wave has several ids and takes registers (130
+// against 48 at NT = 4: two waves per SIMD instead of four) where prefixes,
+// not ids, are many.  From 12 tokens per prefix and 24 ids that a prefix can
+// have; the whole backward, plain against AHEAD: 12000 uniform ids of a 30 x
+// 31 x 33 table (13 per prefix) 113.0 against 111.2 us, 3000 ids (3.2) 81.5
+// against 84.9; 40000 ids of a 60 x 60 x 16 table (11, at most 16) 211.9 against
+// 227.7, 5000 ids of a 14 x 13 x 14 x 13 table 102.2 against 110.4.  Between 8
+// and 12 per prefix the workgroups' rounds decide (1092 prefixes, 9000 ids: the
+// kernel 35.1 against 38.0 us).
+template <int NT, int NKS, bool AHEAD>
 __global__ __launch_bounds__(256) void embed_dapre_mfma_kernel(const int *__restrict__ headpos,
                                                                const float *__restrict__ S,
                                                                const float *__restrict__ Gs, int64_t Vp, int R,
@@ -913,44 +924,69 @@ __global__ __launch_bounds__(256) void embed_dapre_mfma_kernel(const int *__rest
     for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int c = 0; c < 2; ++c) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // the next id's operands load while the current ones are multiplied
-    float sa[2][NT][NKS], gb[2][2][NKS];
-    // (masked when they are used: masking waits for the load)
-    auto load = [&](int u, float (&x)[NT][NKS], float (&y)[2][NKS]) {
-        const int vs = vsl[u];
-        const float *su = S + int64_t(hpl[u]) * E;
+    if constexpr (AHEAD) {
+        float sa[2][NT][NKS], gb[2][2][NKS];
+        // (masked when they are used: masking waits for the load)
+        auto load = [&](int u, float (&x)[NT][NKS], float (&y)[2][NKS]) {
+            const int vs = vsl[u];
+            const float *su = S + int64_t(hpl[u]) * E;
 #pragma unroll
-        for (int k = 0; k < NKS; ++k) {
-            const int ec = min(NKS * q + k, Es - 1);
+            for (int k = 0; k < NKS; ++k) {
+                const int ec = min(NKS * q + k, Es - 1);
 #pragma unroll
-            for (int t = 0; t < NT; ++t) x[t][k] = su[(16 * t + r) * Es + ec];
+                for (int t = 0; t < NT; ++t) x[t][k] = su[(16 * t + r) * Es + ec];
 #pragma unroll
-            for (int c = 0; c < 2; ++c) y[c][k] = Gs[(int64_t(min(16 * c + r, R - 1)) * Vs + vs) * Es + ec];
-        }
-    };
-    auto madd = [&](const float (&x)[NT][NKS], const float (&y)[2][NKS]) {
-#pragma unroll
-        for (int k = 0; k < NKS; ++k) {
-            const uint32_t me = mask_if(NKS * q + k < Es);
-            float yc[2];
-#pragma unroll
-            for (int c = 0; c < 2; ++c) yc[c] = masked(y[c][k], me & mask_if(16 * c + r < R));
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const float xt = masked(x[t][k], me);
-#pragma unroll
-                for (int c = 0; c < 2; ++c)
-                    acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(xt, yc[c], acc[t][c], 0, 0, 0);
+                for (int c = 0; c < 2; ++c) y[c][k] = Gs[(int64_t(min(16 * c + r, R - 1)) * Vs + vs) * Es + ec];
             }
+        };
+        auto madd = [&](const float (&x)[NT][NKS], const float (&y)[2][NKS]) {
+#pragma unroll
+            for (int k = 0; k < NKS; ++k) {
+                const uint32_t me = mask_if(NKS * q + k < Es);
+                float yc[2];
+#pragma unroll
+                for (int c = 0; c < 2; ++c) yc[c] = masked(y[c][k], me & mask_if(16 * c + r < R));
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const float xt = masked(x[t][k], me);
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+                        acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(xt, yc[c], acc[t][c], 0, 0, 0);
+                }
+            }
+        };
+        if (u0 < u1) load(u0, sa[0], gb[0]);
+        for (int u = u0; u < u1; u += 2) {
+            if (u + 1 < u1) load(u + 1, sa[1], gb[1]);
+            madd(sa[0], gb[0]);
+            if (u + 1 >= u1) break;
+            if (u + 2 < u1) load(u + 2, sa[0], gb[0]);
+            madd(sa[1], gb[1]);
         }
-    };
-    if (u0 < u1) load(u0, sa[0], gb[0]);
-    for (int u = u0; u < u1; u += 2) {
-        if (u + 1 < u1) load(u + 1, sa[1], gb[1]);
-        madd(sa[0], gb[0]);
-        if (u + 1 >= u1) break;
-        if (u + 2 < u1) load(u + 2, sa[0], gb[0]);
-        madd(sa[1], gb[1]);
+    } else {
+        for (int u = u0; u < u1; ++u) {
+            const int vs = vsl[u];
+            const float *su = S + int64_t(hpl[u]) * E;
+            float x[NT][NKS], y[2][NKS];
+#pragma unroll
+            for (int k = 0; k < NKS; ++k) {
+                const int es = NKS * q + k;
+#pragma unroll
+                for (int t = 0; t < NT; ++t) x[t][k] = es < Es ? su[(16 * t + r) * Es + es] : 0.f;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const int a = 16 * c + r;
+                    y[c][k] = (es < Es && a < R) ? Gs[(int64_t(a) * Vs + vs) * Es + es] : 0.f;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < NKS; ++k)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+                        acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t][k], y[c][k], acc[t][c], 0, 0, 0);
+        }
     }
     // waves 1..3 hand their sums to wave 0, which adds them in wave order
     for (int w = 1; w < 4; ++w) {
@@ -1115,11 +1151,15 @@ void launch_rows_nj(int nj4, dim3 grid, void *stream, const int64_t *ids, int64_
 template <int NT, bool AHEAD>
 void launch_rows_ns(int ns, dim3 grid, void *stream, const int64_t *ids, int64_t n, int64_t V, const float *Apre,
                     const float *Gs, float *Y, int R, int Vs, int Es, int sE, int sR, int *err_flag) {
+    auto go = [&](auto kern) {
+        COMERA_LAUNCH_NAMED(AHEAD ? "embed_rows_mfma_kernel<ahead>" : "embed_rows_mfma_kernel", kern, grid, dim3(256), 0,
+                            hipStream_t(stream), ids, n, V, Apre, Gs, Y, R, Vs, Es, sE, sR, err_flag);
+    };
     switch (ns) {
-        case 1: COMERA_LAUNCH((embed_rows_mfma_kernel<NT, 1, AHEAD>), grid, dim3(256), 0, hipStream_t(stream), ids, n, V, Apre, Gs, Y, R, Vs, Es, sE, sR, err_flag); break;
-        case 2: COMERA_LAUNCH((embed_rows_mfma_kernel<NT, 2, AHEAD>), grid, dim3(256), 0, hipStream_t(stream), ids, n, V, Apre, Gs, Y, R, Vs, Es, sE, sR, err_flag); break;
-        case 4: COMERA_LAUNCH((embed_rows_mfma_kernel<NT, 4, AHEAD>), grid, dim3(256), 0, hipStream_t(stream), ids, n, V, Apre, Gs, Y, R, Vs, Es, sE, sR, err_flag); break;
-        default: COMERA_LAUNCH((embed_rows_mfma_kernel<NT, 8, AHEAD>), grid, dim3(256), 0, hipStream_t(stream), ids, n, V, Apre, Gs, Y, R, Vs, Es, sE, sR, err_flag); break;
+        case 1: go(embed_rows_mfma_kernel<NT, 1, AHEAD>); break;
+        case 2: go(embed_rows_mfma_kernel<NT, 2, AHEAD>); break;
+        case 4: go(embed_rows_mfma_kernel<NT, 4, AHEAD>); break;
+        default: go(embed_rows_mfma_kernel<NT, 8, AHEAD>); break;
     }
 }
 
@@ -1204,13 +1244,16 @@ int launch_embed_segsum(const float *dY, int E, int n, int passes, const EmbedWs
     return launch_status();
 }
 
-int launch_embed_dapre(const EmbedWs &w, const float *Gs, int64_t Vp, int Ep, int R, int Vs, int Es, int vq, int eq,
+int launch_embed_dapre(const EmbedWs &w, int64_t n, const float *Gs, int64_t Vp, int Ep, int R, int Vs, int Es, int vq, int eq,
                        void *stream) {
     if (Ep % 16 == 0 && Ep <= 64 && R <= 32 && Es <= 16 && Vs <= 1024) {
         const dim3 grid(static_cast<unsigned>(Vp), 1, 1);
-#define COMERA_DAPRE(NT, NK)                                                                                     \
-    COMERA_LAUNCH((embed_dapre_mfma_kernel<NT, NK>), grid, dim3(256), 0, hipStream_t(stream), w.headpos, w.S, \
-                       Gs, Vp, R, Vs, Es, vq, eq, w.dA)
+        const bool ahead = Vs >= 24 && n >= 12 * Vp;
+        auto go = [&](auto kern) {
+            COMERA_LAUNCH_NAMED(ahead ? "embed_dapre_mfma_kernel<ahead>" : "embed_dapre_mfma_kernel", kern, grid,
+                                dim3(256), 0, hipStream_t(stream), w.headpos, w.S, Gs, Vp, R, Vs, Es, vq, eq, w.dA);
+        };
+#define COMERA_DAPRE(NT, NK) (ahead ? go(embed_dapre_mfma_kernel<NT, NK, true>) : go(embed_dapre_mfma_kernel<NT, NK, false>))
         const int nk = (Es + 3) / 4;
         switch (Ep / 16) {
             case 1: if (nk <= 2) COMERA_DAPRE(1, 2); else COMERA_DAPRE(1, 4); break;

@@ -160,3 +160,36 @@ def test_reuse_forward_and_hot_prefix(case):
     dGr = OE.backward(ids, dY, cores, D)
     for k in range(len(v)):
         assert rel_err(to_np(a[k]), dGr[k]) <= 1e-4, k
+
+
+AHEAD = [
+    # (v, e, r): E_p = 16, 32, .. 128; E_last 4 to 16; ranks on both sides of 4, 8, 16 and 32, whole products
+    # of four ranks left out; more and fewer than 24 ids under a prefix
+    ((6, 5, 24), (4, 4, 7), (1, 3, 3, 1)),
+    ((6, 5, 25), (4, 8, 16), (1, 4, 17, 1)),
+    ((3, 7, 31), (4, 12, 12), (1, 6, 9, 1)),
+    ((5, 4, 32), (8, 8, 4), (1, 8, 32, 1)),
+    ((5, 4, 32), (8, 8, 12), (1, 8, 13, 1)),
+    ((5, 4, 24), (8, 10, 8), (1, 4, 8, 1)),
+    ((4, 9, 16), (8, 12, 5), (1, 5, 30, 1)),
+    ((30, 26), (112, 9), (1, 20, 1)),
+    ((30, 23), (128, 8), (1, 31, 1)),
+]
+
+
+@pytest.mark.parametrize("case", AHEAD, ids=["x".join(map(str, c[1])) + f"r{c[2][-2]}" for c in AHEAD])
+def test_loads_ahead(case):
+    """From 4096 ids the rows' operands, and from 12 tokens per prefix the dA
+    sums', are all loaded before the first product, at clamped indices and
+    masked: the oracle's rows and gradients, and bit for bit the rows of calls
+    below that count."""
+    import torch
+    v, e, r = case
+    T = 4099
+    print(f"embed ahead {case}", flush=True)
+    cores, D, ids, dY = _problem(31 + sum(e), v, e, r, T)
+    run, ids_t, _ = _check(v, e, r, cores, D, ids, dY)
+    Y = run.forward(ids_t)
+    few = EmbedRun(v, e, r, cores, D, 2000)
+    for i in (0, T - 2000):
+        assert torch.equal(few.forward(ids_t[i:i + 2000].contiguous()), Y[i:i + 2000])

@@ -172,3 +172,36 @@ def test_maximum_pass_leaves_no_workgroup_without_loads(act, rows, cols, name, n
     assert (log[0]["kernel"], log[0]["grid"][0]) == (name, nb)
     chunks = rows * cols // (8 if act == "bf16" else 4)
     assert (nb - 1) * 1024 * (8 if "wide" in name else 4) < chunks
+
+
+# ------------------------------------------------------------------ embedding
+@pytest.mark.parametrize("v,n,rows_ahead,da_ahead", [
+    ((30, 31, 33), 4095, False, False), ((30, 31, 33), 4096, True, False), ((30, 31, 33), 12 * 930, True, True),
+    ((30, 31, 24), 12 * 930, True, True), ((30, 31, 23), 12 * 930, True, False), ((30, 31, 33), 12 * 930 - 1, True, False),
+    ((4, 5, 32), 240, False, True),
+])
+def test_embedding_loads_ahead(v, n, rows_ahead, da_ahead):
+    e, r = (8, 8, 12), (1, 30, 30, 1)
+    s = C.tt_embed_shape(v, e, r)
+    wsb = C.comera_tt_embed_workspace_bytes(s, n)
+    G, dG = (C._ptr_array([fake(4 * r[k] * v[k] * e[k] * r[k + 1]) for k in range(3)]) for _ in range(2))
+    ids, Y, dY, ws, lib = fake(8 * n), fake(4 * n * 768), fake(4 * n * 768), fake(wsb), C.load()
+    C.comera_debug_launch_check(True)
+    try:
+        assert lib.comera_tt_embed_forward(s, ids, n, G, None, Y, ws, wsb, None, 0) == C.OK
+        assert lib.comera_tt_embed_backward(s, ids, n, dY, G, None, dG, 1, ws, wsb, None, 0) == C.OK
+        names = [x["kernel"] for x in C.comera_debug_launch_log()]
+    finally:
+        C.comera_debug_launch_check(False)
+    assert ("embed_rows_mfma_kernel<ahead>" in names, "embed_rows_mfma_kernel" in names) == (rows_ahead, not rows_ahead)
+    assert ("embed_dapre_mfma_kernel<ahead>" in names, "embed_dapre_mfma_kernel" in names) == (da_ahead, not da_ahead)
+
+
+def test_embedding_loads_ahead_in_the_gpu_cases():
+    """The GPU parity cases take the rows' loads ahead in every form, and both
+    forms of dA."""
+    from tests.test_gpu_embed import AHEAD
+    assert {math.prod(e[:-1]) // 16 for _, e, _ in AHEAD} == set(range(1, 9))
+    assert {(r[-2] + 3) // 4 > 4 for _, _, r in AHEAD} == {True, False}
+    assert {v[-1] >= 24 for v, _, _ in AHEAD} == {True, False}
+    assert all(4099 >= 12 * math.prod(v[:-1]) for v, _, _ in AHEAD)
