@@ -656,8 +656,15 @@ comera_status chain_backward(const comera_ttm_plan_s *p, int64_t b, const void *
     a.part = reinterpret_cast<float *>(reinterpret_cast<char *>(ws) + p->ch.part);
     const int grid = int(std::min<int64_t>((b + a.TB - 1) / a.TB, p->ch.grid_b));
     // one workgroup per output while all of them run at once (one per CU: the
-    // states and both core copies take most of its LDS)
-    a.split = int64_t(grid) * (d + 1) <= 256 ? 1 : 0;
+    // states and both core copies take most of its LDS), unless dX is written
+    // over X or dY: one workgroup reads its tokens before it writes them, the
+    // rows of the grid read them while another writes
+    const int64_t esz = p->s.act == COMERA_BF16 ? 2 : 4;
+    auto overlaps = [&](const void *in, int64_t width) {
+        const uintptr_t o = reinterpret_cast<uintptr_t>(dX), i = reinterpret_cast<uintptr_t>(in);
+        return dX && o < i + uintptr_t(b * width * esz) && i < o + uintptr_t(b * p->N_in * esz);
+    };
+    a.split = int64_t(grid) * (d + 1) <= 256 && !overlaps(X, p->N_in) && !overlaps(dY, p->N_out) ? 1 : 0;
     void *ev;
     timing_begin(const_cast<comera_ttm_plan_s *>(p), COMERA_KERNEL_DX, stream, &ev);
     int e = note_hip(launch_chain(a, true, grid, stream), "fused sweep backward");

@@ -205,3 +205,24 @@ def test_embedding_loads_ahead_in_the_gpu_cases():
     assert {(r[-2] + 3) // 4 > 4 for _, _, r in AHEAD} == {True, False}
     assert {v[-1] >= 24 for v, _, _ in AHEAD} == {True, False}
     assert all(4099 >= 12 * math.prod(v[:-1]) for v, _, _ in AHEAD)
+
+
+# ------------------------------------------------------------------ outputs over inputs
+def _backward_log(n, m, r, b, order, over):
+    p = C.TTMPlan(n, m, r, C.F32, batch=b, force_order=order)
+    X, dY, other = (fake(4 * b * math.prod(n)) for _ in range(3))
+    G, dG = (C._ptr_array([fake(4 * r[k] * m[k] * n[k] * r[k + 1]) for k in range(len(n))]) for _ in range(2))
+    C.comera_debug_launch_check(True)
+    try:
+        assert C.load().comera_ttm_backward(p.handle, b, X, dY, G, None, {"X": X, "dY": dY, None: other}[over], dG,
+                                            fake(p.workspace_bytes), p.workspace_bytes, 0) == C.OK
+        return C.comera_debug_launch_log()
+    finally:
+        C.comera_debug_launch_check(False)
+
+
+def test_fused_sweep_backward_in_place_keeps_one_workgroup_per_token_group():
+    n, m, r = (8, 8, 12), (12, 8, 8), (1, 8, 8, 1)
+    rows = {o: [x["grid"][1] for x in _backward_log(n, m, r, 32, 7, o) if "chain_bwd" in x["kernel"]]
+            for o in (None, "X", "dY")}
+    assert rows == {None: [4], "X": [1], "dY": [1]}
