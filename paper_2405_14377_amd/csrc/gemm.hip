@@ -1885,7 +1885,12 @@ bool skinny_ok(const GemmArgs &g) {
     if (g.rmap.nd != 1 || g.cmap.nd != 1 || g.cmap.stride[0] != 1) return false;
     const int64_t e = g.dtype == COMERA_BF16 ? 8 : 4;
     if (g.K % e || g.lda % e || g.ldb % e) return false;
-    return reinterpret_cast<uintptr_t>(g.A) % 16 == 0 && reinterpret_cast<uintptr_t>(g.B) % 16 == 0;
+    // a result written over A (a forward call in place): every workgroup reads
+    // all of A, split K has read it before it sums
+    const uintptr_t a = reinterpret_cast<uintptr_t>(g.A), c = reinterpret_cast<uintptr_t>(g.C);
+    const uintptr_t abytes = uintptr_t(g.M * g.lda) * (16 / e), cbytes = uintptr_t(g.M * g.rmap.stride[0]) * (g.out_bf16 ? 2 : 4);
+    if (a < c + cbytes && c < a + abytes) return false;
+    return a % 16 == 0 && reinterpret_cast<uintptr_t>(g.B) % 16 == 0;
 }
 
 template <typename T, bool OB>

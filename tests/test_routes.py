@@ -226,3 +226,21 @@ def test_fused_sweep_backward_in_place_keeps_one_workgroup_per_token_group():
     rows = {o: [x["grid"][1] for x in _backward_log(n, m, r, 32, 7, o) if "chain_bwd" in x["kernel"]]
             for o in (None, "X", "dY")}
     assert rows == {None: [4], "X": [1], "dY": [1]}
+
+
+def test_forward_in_place_keeps_split_k():
+    n, m, r, b = (8, 8, 12), (12, 8, 8), (1, 6, 7, 1), 16
+    p = C.TTMPlan(n, m, r, C.BF16, batch=b, force_order=0)
+    X, Y = fake(2 * b * 768), fake(2 * b * 768)
+    G = C._ptr_array([fake(4 * r[k] * m[k] * n[k] * r[k + 1]) for k in range(3)])
+    names = {}
+    for key, out in (("apart", Y), ("in place", X)):
+        C.comera_debug_launch_check(True)
+        try:
+            assert C.load().comera_ttm_forward(p.handle, b, X, G, None, out, fake(p.workspace_bytes),
+                                               p.workspace_bytes, 0) == C.OK
+            names[key] = [x["kernel"] for x in C.comera_debug_launch_log()]
+        finally:
+            C.comera_debug_launch_check(False)
+    assert "gemm_skinny_kernel" in names["apart"] and "gemm_skinny_kernel" not in names["in place"]
+    assert any("sum_splits" in k for k in names["in place"])
