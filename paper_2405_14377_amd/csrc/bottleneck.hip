@@ -8,7 +8,8 @@
 // a pass reads its input once, keeps its R-wide state in LDS between the two
 // products and writes its output once, and the meets read X and dY once more.
 // Launches per training step: build, pass (Y), pass (dX), meet, split sum,
-// core gradients.  The general sweep (one GEMM per product on tiles made for
+// core gradients.  Sweeps of this kind outside faster_here keep the general
+// route (sweep.hip).  The general sweep (one GEMM per product on tiles made for
 // square operands, and one kernel per core and step of the batch-free work)
 // took 17 launches and 535 us on 1024 -> 4096, r = 32, 40000 tokens in bf16
 // and 205 us on 768 -> 3072, r = 30, 4096 tokens in fp32; this one 331 and
@@ -875,8 +876,12 @@ int go_pass(const PassArgs &a, int RP, void *stream) {
         COMERA_LAUNCH_NAMED("tt_pass_kernel", kern, grid, dim3(64 * kPassWaves), 0, hipStream_t(stream), a);
         return launch_status();
     };
-    // the largest tile that leaves no CU without a workgroup; 64 tokens of a
-    // 64-wide state would not fit two workgroups' LDS on a CU
+    // the largest tile that leaves no CU without a workgroup (a step of 768 ->
+    // 3072 by tokens a tile, 16 / 32 / 64: r30 fp32 8192 tokens 152 / 141 / 192
+    // us, 16384 tokens 274 / 249 / 243, 65536 tokens 939 / 858 / 800; r48 bf16
+    // 4096 tokens 100 / 104 / 115, 8192 tokens 130 / 113 / 123).  That is so
+    // also for fp32's 64-token tile, whose 81 KiB of LDS leave one workgroup to a
+    // CU (bf16 77 KiB: two).  A 64-wide state stops at 32 tokens.
     const int64_t blocks = (a.b + 15) / 16;
     if (RP == 32) {
         if (blocks >= 4 * 256) return go(tt_pass_kernel<T, 32, 4>, 4);

@@ -1711,10 +1711,10 @@ int launch_fast(const GemmArgs &g, const GemmParams &p, int id, void *stream) {
 // take 64-byte rows.  Returns -1 when the product is too small to fill the
 // chip with these tiles (the general kernel's smaller tiles do better).
 int pick_fast(const GemmArgs &g, int splits) {
-    // transposed operands with a side of 64 or less (the meets of the paper's
-    // TT layout) stream the token rows: these tiles would mostly compute
-    // padding, the general kernel's 32-wide skinny tiles do better (the
-    // sweep steps of that layout are measured on its 1024 -> 4096 shape)
+    // transposed operands with a side of 64 or less (the meets of a sweep
+    // through a narrow bond that keeps the general route) stream the token
+    // rows: these tiles would mostly compute padding, the general kernel's
+    // 32-wide skinny tiles do better
     if (!g.a_kc && !g.b_kc && (g.M <= 64 || g.N <= 64) && g.dtype != kDtypeFp8) return -1;
     // K-contiguous operands with a side of 64 or less: the tile whose short
     // side is 64

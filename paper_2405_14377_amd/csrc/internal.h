@@ -85,21 +85,6 @@ struct Fp8Layout {
 };
 constexpr int kScW = 0, kScX = 1, kScDY = 2, kScFwd = 3, kScDX = 4, kScDW = 5;
 
-// Sweep orders (groups of consecutive cores, activations swept through the
-// groups in sequence).  Each group g (cores s[g] .. e[g]) is treated as a
-// layer of its own whose outer bonds are folded into its outer factors:
-//   right to left:  W'_g [(N_g, ae_g)][(as_g, M_g)]
-//   left to right:  W'_g [(as_g, N_g)][(M_g, ae_g)]
-// where N_g, M_g are the products of the group's input and output factors
-// and as_g, ae_g its left and right (compacted) bond ranks.  The states of
-// both sweeps are stored with the next contraction's index last:
-//   right to left, activation state Z_g (input of step g-1):
-//       [(b, N_<g-1, M_>=g)][(N_{g-1}, ae_{g-1})]
-//   right to left, dY state H_g (input of step g): [(b, N_<g, M_>g)][(as_g, M_g)]
-//   left to right, activation state Z_g (input of step g): [(b, M_<g, N_>g)][(as_g, N_g)]
-//   left to right, dY state H_g (input of step g): [(b, M_<g, N_>g)][(M_g, ae_g)]
-// so the gradient of W'_g is one product A^T B of the two states that meet
-// at group g, with the token-like index (b and the outer factors) as K.
 // Workspace of the two-group sweep through one bond (bottleneck.hip): chain
 // data of each group (index: group, chain position), the operands of the
 // batch products (op [N][RP], opt in 64-byte pieces of its columns), the states of X
@@ -115,6 +100,22 @@ struct BottleneckLayout {
     size_t keep[kMaxCores] = {};
     size_t total = 0;
 };
+
+// Sweep orders (groups of consecutive cores, activations swept through the
+// groups in sequence).  Each group g (cores s[g] .. e[g]) is treated as a
+// layer of its own whose outer bonds are folded into its outer factors:
+//   right to left:  W'_g [(N_g, ae_g)][(as_g, M_g)]
+//   left to right:  W'_g [(as_g, N_g)][(M_g, ae_g)]
+// where N_g, M_g are the products of the group's input and output factors
+// and as_g, ae_g its left and right (compacted) bond ranks.  The states of
+// both sweeps are stored with the next contraction's index last:
+//   right to left, activation state Z_g (input of step g-1):
+//       [(b, N_<g-1, M_>=g)][(N_{g-1}, ae_{g-1})]
+//   right to left, dY state H_g (input of step g): [(b, N_<g, M_>g)][(as_g, M_g)]
+//   left to right, activation state Z_g (input of step g): [(b, M_<g, N_>g)][(as_g, N_g)]
+//   left to right, dY state H_g (input of step g): [(b, M_<g, N_>g)][(M_g, ae_g)]
+// so the gradient of W'_g is one product A^T B of the two states that meet
+// at group g, with the token-like index (b and the outer factors) as K.
 struct SweepLayout {
     int G = 0;
     int dir = 0;                       // COMERA_ORDER_SWEEP_RL or _LR

@@ -1,7 +1,10 @@
-"""GPU parity of layers over at most 64 tokens, whose forward and dX products
-take the few-rows kernel (dense order): one token up to one past its limit,
-widths that are no whole number of 16 columns or 64-byte steps of K, and a K
-that the eight waves share unevenly; Y, dX and every dG_k against the oracle.
+"""GPU parity of layers over at most 64 tokens in the dense order, whose
+forward and dX products take the few-rows kernel where it is the faster one
+(tests/test_routes.py: which of them do, in every form of 16, 32 and 64 rows;
+an fp32 dX over 1024 or more outputs keeps the plan's splits of K): one token
+up to one past its limit, widths that are no whole number of 16 columns or
+64-byte steps of K, and a K that the eight waves share unevenly; Y, dX and
+every dG_k against the oracle.
 
 Tolerance as for the layers: max |gpu - ref| / max |ref| <= 1e-4 (fp32),
 <= 2e-2 (bf16).

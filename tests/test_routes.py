@@ -95,6 +95,22 @@ def test_one_bond_kernels_where_they_are_faster(act, ins, outs, rank, b, own):
         assert not [k for k in fwd + bwd if k.startswith("tt_")]
 
 
+def test_one_bond_kernels_of_the_gpu_cases():
+    """The GPU parity cases reach the kernels that they are for."""
+    from tests.test_gpu_bottleneck import SHAPES, _layout
+    cases = [(ins, outs, ranks, b) for _, ins, outs, ranks, b in SHAPES]
+    cases += [((8, 4), (4, 16), (6, 10, 6), b) for b in (8200, 16400)]
+    cases += [((4, 3, 4), (4, 4, 3), (4, 12, 40, 12, 4), 200), ((4, 4, 6), (6, 4, 4), (5, 6, 7, 6, 5), 90)]
+    cases += [((4, 6), (8, 4), x, 72) for x in ((3, 1, 2), (6, 30, 7), (6, 33, 7))]
+    for ins, outs, ranks, b in cases:
+        n, m, r = _layout(ins, outs, ranks)
+        desc = _tt(ins, outs, 1)[3]
+        for act in ("f32", "bf16"):
+            fwd, bwd, _ = layer_kernels(n, m, r, act, b, desc)
+            assert fwd == ["tt_build_kernel", "tt_pass_kernel"], (ins, outs, ranks, b, act)
+            assert "tt_meet_kernel" in bwd and "tt_grad_kernel" in bwd
+
+
 # ------------------------------------------------------------------ products of few rows
 _F = {512: (8, 8, 8), 768: (8, 8, 12), 1000: (10, 10, 10), 1024: (8, 8, 16), 1280: (8, 10, 16), 1536: (8, 12, 16),
       2048: (8, 16, 16), 3072: (16, 16, 12), 4096: (16, 16, 16), 8192: (16, 16, 32), 16384: (32, 16, 32),
@@ -117,6 +133,16 @@ _F = {512: (8, 8, 8), 768: (8, 8, 12), 1000: (10, 10, 10), 1024: (8, 8, 16), 128
 def test_few_rows_kernel_where_it_is_faster(act, K, N, b, own):
     fwd, _, _ = layer_kernels(_F[K], _F[N], (1, 4, 4, 1), act, b, 0)
     assert ("gemm_skinny_kernel" in fwd) == own
+
+
+def test_few_rows_kernel_of_the_gpu_cases():
+    """The GPU parity cases reach every form of the kernel: 16, 32 and 64 rows
+    in both dtypes, K and N that are no whole number of steps or tiles."""
+    from tests.test_gpu_skinny import SHAPES
+    own = {(act, b, i) for act in ACT for b in (1, 7, 16, 17, 32, 33, 64, 65) for i, (n, m) in enumerate(SHAPES)
+           if "gemm_skinny_kernel" in layer_kernels(n, m, (1, 6, 7, 1), act, b, 0)[0]}
+    assert {(act, b) for act, b, _ in own} == {(act, b) for act in ACT for b in (1, 7, 16, 17, 32, 33, 64)}
+    assert {i for _, b, i in own if b <= 16} == {0, 1, 2} and {i for a, b, i in own if a == "bf16" and b > 32} == {0, 1}
 
 
 def test_few_rows_dx_keeps_the_splits_of_the_plan():
